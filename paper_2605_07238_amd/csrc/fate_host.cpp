@@ -1116,6 +1116,18 @@ static void sim_fill(const fate_dags_t *dags, const fate_state_h *state, float k
     a.B = state->B;
     a.D = dags->D;
     a.K = state->K;
+    a.M = dags->M;
+    a.ch_off = dags->ch_off;
+    a.max_stages = dags->max_stages;
+    a.beta_uniform = dags->beta_uniform;
+    a.beta0 = dags->beta0;
+    // the mean of D (D - 1) equal coefficients, summed one by one as for others
+    a.bmean = 0.0;
+    if (dags->beta_uniform && dags->D > 1) {
+        const int pairs = dags->D * (dags->D - 1);
+        for (int i = 0; i < pairs; ++i) a.bmean += (double)dags->beta0;
+        a.bmean /= (double)pairs;
+    }
 }
 
 extern "C" {

@@ -274,7 +274,12 @@ struct SimLaunch {
     uint32_t *ids, *todo;
     uint8_t *flags;
     double kpf;
-    int32_t B, D, K;
+    const uint32_t *ch_off;  // stage g has children if ch_off[g] < ch_off[g + 1]
+    int64_t max_stages;      // stages of the largest instance
+    double bmean;            // mean off-diagonal transfer coefficient (uniform beta)
+    float beta0;             // every off-diagonal coefficient (uniform beta)
+    int32_t beta_uniform;
+    int32_t B, D, K, M;
 };
 struct SimWs {
     size_t fin, aux, tail, hold, keys, ids, todo, flags, total;

@@ -185,3 +185,58 @@ def test_device_full_batch_forkjoin():
     host = fate.fate_simulate(w, hdev, hord)
     for k in got:
         assert np.array_equal(got[k], host[k]), k
+
+
+def _fan_in_batch(fans, D, M, K, tiered, seed):
+    """Per fan-in one instance: roots (some completed, some pending), a join of
+    all of them, and children of the join, with repeated groups in the prefix
+    slots and models that do not fit beside each other."""
+    import builders
+    rng = np.random.default_rng(seed)
+    insts = []
+    for fan in fans:
+        parents = [[] for _ in range(fan)] + [list(range(fan))] + [[fan]] * 3 + [[fan + 1, fan + 2, fan + 3]]
+        n = len(parents)
+        done = [int(v < fan // 3) for v in range(n)]
+        insts.append(dict(
+            parents=parents, model=rng.integers(0, M, n).tolist(), elig=[(1 << D) - 1] * n,
+            prefix_hash=rng.integers(0, 6, n).tolist(), prefix_tokens=(rng.integers(1, 30, n) * 100.0).tolist(),
+            out_bytes=(rng.integers(1, 9, n) * 1e8).tolist(), status=done,
+            holders=[(1 << int(rng.integers(D))) * d for d in done], resident=rng.integers(0, 4, D).tolist(),
+            prefix_cache=rng.integers(0, 6, (D, K)).tolist(), tau_free=rng.random(D).tolist(), t_now=0.25))
+    beta = rng.integers(1, 5, (D, D)) * 1e-10 if tiered else np.full((D, D), 2e-10)
+    np.fill_diagonal(beta, 0.0)
+    spec = dict(D=D, M=M, K=K, exec=(rng.integers(1, 9, (M, D)) / 4).tolist(), switch_s=(rng.integers(0, 3, (M, D)) / 8).tolist(),
+                weight_gb=rng.integers(8, 20, M).tolist(), cap_gb=[32] * D, beta=beta.tolist(), max_shard=1, instances=insts)
+    return builders.from_spec(spec, H=0)
+
+
+@pytest.mark.parametrize("name,make", [
+    ("fans-d4", lambda: _fan_in_batch([0, 1, 4, 5, 16, 17, 58, 59, 60, 64, 65, 130, 300], 4, 3, 2, False, 1)),
+    ("fans-d20-tiered", lambda: _fan_in_batch([1, 4, 5, 16, 17, 64, 65, 200], 20, 5, 3, True, 2)),
+    ("fans-d64-k32", lambda: _fan_in_batch([3, 40, 65, 100], 64, 33, 32, False, 3)),
+    ("no-slots", lambda: _fan_in_batch([7, 90], 9, 4, 0, False, 4)),
+    ("lds-5000", lambda: _fan_in_batch([4995], 16, 6, 16, False, 5)),
+    ("workspace-8200", lambda: _fan_in_batch([8195], 16, 6, 16, False, 6)),
+], ids=lambda x: x if isinstance(x, str) else "")
+def test_device_walk_edges(name, make):
+    """Batches of 64 stages, prefetched and unprefetched parent lists, one
+    parent to several hundred, repeated prefix slots, evictions; instances in
+    LDS and past it.  Placements and metrics equal the host executor's to the
+    bit (the same fp64 operations), on HEFT and round-robin plans and on
+    windows."""
+    w = make()
+    pk, st = _packed(w)
+    print("[sim] walk edges", name, flush=True)
+    kpf = w.params["kappa_prefix"]
+    dt, ot = fate.fate_place_baseline_device(pk, st, fate.FATE_PLACE_HEFT, kpf)
+    hdev, hord = fate.fate_place_baseline(w, fate.FATE_PLACE_HEFT)
+    assert np.array_equal(dt.cpu().numpy().view(np.uint64), hdev) and np.array_equal(ot.cpu().numpy(), hord)
+    rng = np.random.default_rng(9)
+    width = rng.integers(1, min(4, w.D) + 1, w.N)
+    first = np.array([int(rng.integers(0, w.D - k + 1)) for k in width])
+    wide = np.array([((1 << int(k)) - 1) << int(i) for k, i in zip(width, first)], np.uint64) * (hdev != 0)
+    for dev, order in ((hdev, hord), fate.fate_place_baseline(w, fate.FATE_PLACE_ROUND_ROBIN), (wide, hord)):
+        got, host = _run_device(w, pk, st, dev, order), fate.fate_simulate(w, dev, order)
+        for k in got:
+            assert np.array_equal(got[k], host[k]), k
