@@ -84,7 +84,8 @@ struct StageL {
     uint32_t v, e0, e1, dbeg;
     uint32_t c0, nc;      // first score and number of candidates
     uint16_t dn, npar;
-    uint8_t model, shard, pad0, pad1;
+    uint8_t model, shard;
+    uint8_t part0, parts; // one-shot slices: the first group scoring its rows, and how many do
     uint64_t pfm;         // devices caching grp(v), looked up once the prefix table is built
 };
 static_assert(sizeof(StageL) == 64, "StageL");
@@ -190,7 +191,22 @@ struct alignas(16) CostS {
 struct LdsPlan {
     uint32_t pkey, pmask, rm, rho, fits, wt, cap, order, wait, gpow, next, exec, ksw, stages, entries, total;
     uint32_t items, parts, left, pbase, plen, pool;  // row splits of heavy stages (64-lane groups)
+    uint32_t rnew;              // general layout, at most 32 devices: residency after each load
+    uint32_t btab, brow, bstr;  // non-uniform beta, at most 32 devices: see beta_table
 };
+
+// Rows of the transfer table (non-uniform beta, at most 32 devices; a loop over
+// the devices with shuffles and global loads per candidate before it: 333
+// layered instances on 24 devices with tiered links and windows, 206 us, 71 with
+// the table and the rows dealt out, 38 with the windows on fixed lanes): row j
+// holds, per device d, the cheapest coefficient from a device of candidate j
+// into d (+infinity on the candidate's own devices), for the singles and then
+// the windows of 2 to 4 devices.
+__host__ __device__ inline int beta_rows(int D) {
+    int n = D;
+    for (int k = 2; k <= FATE_MAX_SHARD && k <= D; ++k) n += D - k + 1;
+    return n;
+}
 
 // 64-lane groups: a singletons-only stage with more than kSplitRows
 // descendant rows is scored in parts of kSplitRows rows by several waves of
@@ -202,7 +218,8 @@ struct LdsPlan {
 constexpr int kSplitRows = 128, kSplitItems = 256, kSplitSlots = 32;
 static_assert(kSplitRows % 64 == 0, "a part is whole 64-row batches");
 
-__host__ __device__ inline LdsPlan lds_plan(int D, int K, int M, int slice, int staging, bool slots, bool split) {
+__host__ __device__ inline LdsPlan lds_plan(int D, int K, int M, int slice, int staging, bool slots, bool split,
+                                            bool uni, int blk) {
     LdsPlan q;
     const uint32_t T = 1u << table_log2(D, K);
     const uint32_t mask_bytes = D <= 32 ? 4u : 8u;
@@ -230,6 +247,17 @@ __host__ __device__ inline LdsPlan lds_plan(int D, int K, int M, int slice, int 
     } else {  // [M][D] execution times and weighted switch times
         q.exec = o; o += 4 * (uint32_t)(M * D);
         q.ksw = o; o += 4 * (uint32_t)(M * D);
+    }
+    q.rnew = q.btab = q.brow = o;
+    q.bstr = (((uint32_t)D + 3u) & ~3u) + 4u;  // whole float4s; consecutive rows start on different banks
+    if (!slots && D <= 32) {
+        o = (o + 15u) & ~15u;
+        q.rnew = o; o += 8 * (uint32_t)(M * D);
+        if (!uni) {
+            o = (o + 15u) & ~15u;
+            q.btab = o; o += 4 * q.bstr * (uint32_t)beta_rows(D);
+            q.brow = o; o += 4 * (uint32_t)blk;  // a row of B per lane group
+        }
     }
     q.items = q.parts = q.left = q.pbase = q.plen = q.pool = o;
     if (split) {  // items (position | part << 8), parts, parts left, first pool slot, rows per part, then the pool
@@ -409,18 +437,16 @@ __device__ __forceinline__ void scan_min_pair(float &p0, float &q0, float &p1, f
 template <int G>
 __device__ __forceinline__ float from_left(float x, int lane) {
     if constexpr (G == 16) return dpp_move<0x111>(inf_f(), x);
-    float y;
-    if constexpr (G < 16) y = dpp_move<0x111>(inf_f(), x);
-    else y = __shfl_up(x, 1, G);
+    if constexpr (G == 64) return dpp_move<0x138>(inf_f(), x);  // wave_shr:1
+    const float y = G < 16 ? dpp_move<0x111>(inf_f(), x) : dpp_move<0x138>(inf_f(), x);
     return lane >= 1 ? y : inf_f();
 }
 
 template <int G>
 __device__ __forceinline__ float from_right(float x, int lane) {
     if constexpr (G == 16) return dpp_move<0x101>(inf_f(), x);
-    float y;
-    if constexpr (G < 16) y = dpp_move<0x101>(inf_f(), x);
-    else y = __shfl_down(x, 1, G);
+    if constexpr (G == 64) return dpp_move<0x130>(inf_f(), x);  // wave_shl:1
+    const float y = G < 16 ? dpp_move<0x101>(inf_f(), x) : dpp_move<0x130>(inf_f(), x);
     return lane + 1 < G ? y : inf_f();
 }
 
@@ -623,16 +649,6 @@ __device__ __forceinline__ void rank_stages(const float *scores, const uint32_t 
     }
 }
 
-// One completed parent's contribution on device d: its output is local
-// (colocation count) or has to be transferred from the cheapest holder.
-template <bool UNI>
-__device__ __forceinline__ void add_parent(const ScoreLaunch &a, uint64_t hu, float su, int d, float &tr, float &cnt) {
-    const bool local = bit(hu, d);
-    const float bm = UNI ? a.beta0 : min_beta_into(a.beta, hu, d, a.D);
-    cnt += local ? 1.0f : 0.0f;
-    tr += local ? 0.0f : su * bm;
-}
-
 // Is horizon stage w (record rw, at `depth`) a child of the frontier stage v?
 // With hop levels exactly the depth-1 stages are.  With topological levels a
 // child can sit deeper (another of its parents may have a higher level), so
@@ -652,7 +668,8 @@ __device__ __forceinline__ bool child_of(const ScoreLaunch &a, const StageRec &r
 // first of (split, score_block(G)), (no split, score_block(G)), (no split,
 // half that) whose LDS plan fits a workgroup.
 template <int G, bool UNI, bool SLOTS, bool VAR, bool SPLIT, int BLK>
-__global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(SLOTS ? 5 : BLK == 512 && G == 64 ? 2 : 4)))
+void k_score(ScoreLaunch a) {
     constexpr int kBlock = BLK;  // threads of this workgroup
     static_assert(!SLOTS || (UNI && G == 16), "the slot layout needs 16-lane groups and uniform beta");
     static_assert(!SPLIT || (G == 64 && !SLOTS), "heavy-stage parts are for 64-lane groups");
@@ -678,7 +695,19 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
     constexpr bool kSlots = SLOTS;
     using Entry = EntryL<Mask>;
     constexpr bool kSplit = SPLIT;
-    const LdsPlan plan = lds_plan(D, K, M, a.slice, staging_bytes<G, BLK>(), SLOTS, kSplit);
+    const LdsPlan plan = lds_plan(D, K, M, a.slice, staging_bytes<G, BLK>(), SLOTS, kSplit, UNI, BLK);
+    // non-uniform beta on at most 32 devices: the transfer table
+    constexpr bool kTab = !UNI && G <= 32;
+    float *btab = reinterpret_cast<float *>(sb + plan.btab);
+    const int bstr = (int)plan.bstr;
+    // A slice with no more stages than lane groups is scored in one shot: its
+    // rows are dealt to all groups, a barrier, then one group per stage adds
+    // the parts and emits.  Small slices left half the waves idle, the others
+    // scoring four stages in lockstep: 1,024 layered instances of eight frontier
+    // stages on 16 devices with windows, 24.8 -> 21.3 us.  A workgroup there
+    // spends 6.4 us in its prologue, 7.2 on the rows, 3.8 on the scores and top-k.
+    constexpr int kDeal = kBlock / G < 64 ? kBlock / G : 64;  // groups that rows are dealt to
+    const bool oneshot = !kSplit && nF <= kDeal;
 
     Lds L;
     L.logT = table_log2(D, K);
@@ -732,6 +761,17 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
     } else {
         for (int i = tid; i < M * D; i += kBlock) { L.exec[i] = a.exec[i]; L.ksw[i] = ps.lam_s * a.ksw[i]; }
     }
+    if constexpr (kTab) {
+        const int rows = beta_rows(D);
+        for (int j = tid / G; j < rows; j += kBlock / G) {  // a lane group per row, lane = device
+            int i = j, k = 1;
+            if (j >= D) decode_window(j - D, D, i, k);
+            const int d = tid & (G - 1);
+            float m = inf_f();
+            for (int q = 0; q < k; ++q) m = fminf(m, a.beta[(i + q) * D + (d < D ? d : 0)]);
+            if (d < bstr) btab[j * bstr + d] = d < D && (d < i || d >= i + k) ? m : inf_f();
+        }
+    }
     for (int i = tid; i < P; i += kBlock) {
         uint64_t key = ~0ull;
         if (i < nF) {
@@ -752,7 +792,7 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             st.npar = r.npar;
             st.model = r.model;
             st.shard = r.shard;
-            st.pad0 = st.pad1 = 0;
+            st.part0 = st.parts = 0;
             st.pfm = 0;
             L.stages[i] = st;
             key = ((uint64_t)(0xffffffffu - (st.e1 - st.e0)) << 32) | (uint32_t)i;
@@ -788,6 +828,41 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             rnew[i] = (uint32_t)load_model(L.rho[d], m, L.cap[d], L.wt);
         }
     }
+    if constexpr (!SLOTS && G <= 32) {
+        uint64_t *rnew = reinterpret_cast<uint64_t *>(sb + plan.rnew);
+        for (int i = tid; i < M * D; i += kBlock) {
+            const int m = i / D, d = i - m * D;
+            rnew[i] = load_model(L.rho[d], m, L.cap[d], L.wt);
+        }
+    }
+    if (oneshot) {
+        // parts of L consecutive rows, L the shortest length whose parts (at
+        // least one per stage) are no more than the groups
+        if (tid < 64) {
+            const uint32_t n = tid < nF ? L.stages[tid].e1 - L.stages[tid].e0 : 0u;
+            const uint32_t one = tid < nF ? 1u : 0u;
+            uint32_t R = 0, c = 0;
+            (void)wave_exscan_u32(n, R);
+            uint32_t l0 = max(1u, (R + kDeal - 1u) / kDeal), l1 = max(1u, R);
+            while (l0 < l1) {  // uniform
+                const uint32_t mid = (l0 + l1) >> 1;
+                (void)wave_exscan_u32(max(one, (n + mid - 1u) / mid), c);
+                if (c <= (uint32_t)kDeal) l1 = mid;
+                else l0 = mid + 1u;
+            }
+            const uint32_t np = max(one, (n + l0 - 1u) / l0);
+            const uint32_t p0 = wave_exscan_u32(np, c);
+            if (tid < nF) {
+                L.stages[tid].part0 = (uint8_t)p0;
+                L.stages[tid].parts = (uint8_t)np;
+                for (uint32_t q = 0; q < np; ++q) L.order[p0 + q] = (uint8_t)tid;
+            }
+            if (tid == 0) {
+                L.next[1] = l0;
+                L.next[2] = c;
+            }
+        }
+    } else
     // work order: stage i goes to position = number of keys smaller than its
     // own (keys are distinct), so the most descendants come first
     for (int i = tid; i < nF; i += kBlock) {
@@ -831,7 +906,6 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
     }
     __syncthreads();
 
-    constexpr int kGroups = kBlock / G;
     const int lane = tid & (G - 1);
     const bool live = lane < D;
     const int dl = live ? lane : D - 1;  // clamped device index for table reads
@@ -855,22 +929,65 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
     constexpr int kGpw = 64 / G;  // lane groups per wave
     const int gw = (tid & 63) / G;
     const int nchunks = kSplit ? (int)L.next[1] : (nF + kGpw - 1) / kGpw;
+    int pass = 0;  // one shot: 0 the group's part of the rows, 1 its stage's scores, 2 done
     for (;;) {
-        uint32_t chunk = 0;
-        if ((tid & 63) == 0) chunk = atomicAdd(L.next, 1u);
-        chunk = __builtin_amdgcn_readfirstlane(chunk);
-        if ((int)chunk >= nchunks) break;  // uniform within the wave
-        int pos = (int)chunk * kGpw + gw, part = 0;
-        if constexpr (kSplit) {  // one group per wave: the work item names the position and part
-            const uint32_t item = reinterpret_cast<const uint16_t *>(sb + plan.items)[chunk];
-            pos = (int)(item & 0xffu);
-            part = (int)(item >> 8);
+        int pos = 0, part = 0, si = 0;
+        bool active = true;
+        if (oneshot) {  // uniform over the block
+            const int g = tid / G;
+            if (pass == 2) break;
+            if (pass == 0) {
+                active = g < (int)L.next[2];
+                si = active ? (int)L.order[g] : 0;
+                part = g - (int)L.stages[si].part0;
+            } else {
+                active = g < nF;
+                si = active ? g : 0;
+                pass = 2;
+                if (!active) break;
+            }
+        } else {
+            uint32_t chunk = 0;
+            if ((tid & 63) == 0) chunk = atomicAdd(L.next, 1u);
+            chunk = __builtin_amdgcn_readfirstlane(chunk);
+            if ((int)chunk >= nchunks) break;  // uniform within the wave
+            pos = (int)chunk * kGpw + gw;
+            if constexpr (kSplit) {  // one group per wave: the work item names the position and part
+                const uint32_t item = reinterpret_cast<const uint16_t *>(sb + plan.items)[chunk];
+                pos = (int)(item & 0xffu);
+                part = (int)(item >> 8);
+            }
+            if (pos >= nF) continue;  // the last chunk may be partial
+            si = (int)L.order[pos];
         }
-        if (pos >= nF) continue;  // the last chunk may be partial
-        const int si = (int)L.order[pos];
+        const bool rows_only = oneshot && pass == 0, emits = !rows_only;
         const StageL sv = L.stages[si];
+        // the rows of this item: a stage's, a heavy stage's part, a one-shot part, none
+        const int nparts = kSplit ? (int)(sb + plan.parts)[pos] : 1;
+        const uint32_t plen = kSplit && nparts > 1 ? reinterpret_cast<const uint32_t *>(sb + plan.plen)[pos] : 0u;
+        uint32_t b_lo = sv.e0 + (uint32_t)part * plen;
+        uint32_t b_hi = nparts > 1 ? min(sv.e1, b_lo + plen) : sv.e1;
+        if (oneshot) {
+            b_lo = min(sv.e1, sv.e0 + (uint32_t)part * L.next[1]);
+            b_hi = rows_only && active ? min(sv.e1, b_lo + L.next[1]) : b_lo;
+        }
+        const int dn_v = emits ? (int)sv.dn : 0;  // completed parents for the immediate terms
         const int mv = sv.model;
         const bool hv_cached = bit(sv.pfm, lane);
+
+        // one completed parent's contribution on this lane's device
+        auto parent_on_lane = [&](uint64_t hu, float su, float &t, float &c) {
+            const bool local = bit(hu, dl);
+            float bm = a.beta0;
+            if constexpr (kTab) {
+                bm = inf_f();
+                for (uint32_t h = (uint32_t)hu; h; h &= h - 1u) bm = fminf(bm, btab[__builtin_ctz(h) * bstr + dl]);
+            } else if constexpr (!UNI) {
+                bm = min_beta_into(a.beta, hu, dl, D);
+            }
+            c += local ? 1.0f : 0.0f;
+            t += local ? 0.0f : su * bm;
+        };
 
         // ---- immediate terms of v on device `lane` and the post-state there
         float tr = 0.0f, cnt = 0.0f;
@@ -880,7 +997,7 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
         uint32_t par_h = 0u;
         float par_s = 0.0f;
         if constexpr (kSlots) {
-            if (lane < (int)sv.dn) {
+            if (lane < dn_v) {
                 const DoneParent pu = a.done[sv.dbeg + lane];
                 par_h = (uint32_t)pu.holders;  // at most 16 devices
                 par_s = pu.sigma;
@@ -899,9 +1016,13 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             }
         };
         if constexpr (!kSlots) {  // (the slot layout adds its parents once its first batch is staged)
-            for (int q = 0; q < sv.dn; ++q) {  // uniform trip count
-                const DoneParent pu = a.done[sv.dbeg + q];
-                add_parent<UNI>(a, pu.holders, pu.sigma, dl, tr, cnt);
+            for (int q0 = 0; q0 < dn_v; q0 += 4) {  // uniform trip count; a batch's loads are issued together
+                DoneParent pu[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) pu[j] = a.done[sv.dbeg + min(q0 + j, dn_v - 1)];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (q0 + j < dn_v) parent_on_lane(pu[j].holders, pu[j].sigma, tr, cnt);
             }
         }
         const bool feas_v = live && bit(sv.elig, lane) && bit(L.fits[mv], lane);
@@ -918,7 +1039,8 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
         float a_imm = 0.0f, b_imm = 0.0f;
         if constexpr (!kSlots) imm_terms(a_imm, b_imm);
         const uint64_t rho_new = kSlots ? (uint64_t)reinterpret_cast<const uint32_t *>(L.ksw)[mv * D + dl]
-                                        : load_model(rho, mv, L.cap[dl], L.wt);
+                                 : G <= 32 ? reinterpret_cast<const uint64_t *>(sb + plan.rnew)[mv * D + dl]
+                                           : load_model(rho, mv, L.cap[dl], L.wt);
         const bool prefix_added = sv.hash != 0 && !hv_cached;
         const uint64_t feas_mask = (__ballot(feas_v) >> gbase) & gmask;
 
@@ -928,7 +1050,7 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
         // LDS slots; returns how many entries the batch holds (they form a prefix).
         auto stage_batch = [&](uint32_t base) -> int {
             const uint32_t e = base + lane;
-            bool valid = e < sv.e1;
+            bool valid = e < b_hi;
             uint32_t ent = 0;
             if (valid) {
                 ent = a.desc[e];
@@ -986,10 +1108,10 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
                 }
             } else {
                 float trw = 0.0f, cntw = 0.0f;
-                for (int q = 0; q < ns; ++q) add_parent<false>(a, E.ph[q], E.pw[q], dl, trw, cntw);
+                for (int q = 0; q < ns; ++q) parent_on_lane(E.ph[q], E.pw[q], trw, cntw);
                 for (int q = kCap; q < dn; ++q) {
                     const DoneParent pu = a.done[E.dbeg + q];
-                    add_parent<false>(a, pu.holders, pu.sigma, dl, trw, cntw);
+                    parent_on_lane(pu.holders, pu.sigma, trw, cntw);
                 }
                 X += lam_tr * trw - cntw * cw;
             }
@@ -1023,7 +1145,7 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             };
             auto stage_rows = [&](uint32_t base) -> int {
                 const uint32_t e = base + lane;
-                bool valid = e < sv.e1;
+                bool valid = e < b_hi;
                 uint32_t ent = 0;
                 if (valid) {
                     ent = a.desc[e];
@@ -1091,20 +1213,20 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
 
             // the first batch is staged while v's parent loads are in flight
             int nb_first = 0;
-            if (sv.e0 < sv.e1) nb_first = stage_rows(sv.e0);
-            for (int q0 = 0; q0 < (int)sv.dn; q0 += 16) {  // uniform within the group
+            if (b_lo < b_hi) nb_first = stage_rows(b_lo);
+            for (int q0 = 0; q0 < dn_v; q0 += 16) {  // uniform within the group
                 uint32_t h = par_h;
                 float sg = par_s;
                 if (q0 > 0) {  // rare: more than 16 completed parents
                     h = 0u;
                     sg = 0.0f;
-                    if (q0 + lane < (int)sv.dn) {
+                    if (q0 + lane < dn_v) {
                         const DoneParent pu = a.done[sv.dbeg + q0 + lane];
                         h = (uint32_t)pu.holders;
                         sg = pu.sigma;
                     }
                 }
-                add_parents16(h, sg, min(16, (int)sv.dn - q0));
+                add_parents16(h, sg, min(16, dn_v - q0));
             }
             imm_terms(a_imm, b_imm);
 
@@ -1141,8 +1263,8 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             // Inside S the window minimum of the post-state values slides by one
             // lane per size.  A batch's terms are summed in fp32, batches in fp64.
             double acc0 = 0.0, w_acc[3] = {0.0, 0.0, 0.0};
-            for (uint32_t base = sv.e0; base < sv.e1; base += G) {  // uniform
-                const int nb = base == sv.e0 ? nb_first : stage_rows(base);
+            for (uint32_t base = b_lo; base < b_hi; base += G) {  // uniform
+                const int nb = base == b_lo ? nb_first : stage_rows(base);
                 float f0 = 0.0f, f1 = 0.0f, f2 = 0.0f, f3 = 0.0f;
                 // staged row jj: the key outside S, the value inside S, and gamma^depth.
                 // Branch-free: a bit of a device mask selects a value by masking its bits.
@@ -1251,6 +1373,25 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
                 if (nb < G) break;  // past the horizon depth or the list end
             }
 
+            if (rows_only) {  // uniform over the block: the group leaves its sums in its own staging slots
+                double *sum = reinterpret_cast<double *>(areaS);
+                if (active) {
+                    sum[lane] = acc0;
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) sum[(s + 1) * G + lane] = w_acc[s];
+                }
+                __syncthreads();
+                pass = 1;
+                continue;
+            }
+            if (oneshot)  // the stage's parts in row order
+                for (int q = 0; q < (int)sv.parts; ++q) {
+                    const double *sum = reinterpret_cast<const double *>(static_cast<uint8_t *>(L.entries) + ((int)sv.part0 + q) * kSlotGroupBytes);
+                    acc0 += sum[lane];
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) w_acc[s] += sum[(s + 1) * G + lane];
+                }
+
             // ---- emit scores
             const float psi0 = feas_v ? (float)(-((double)j0_single + acc0)) : -inf_f();
             if (live) scores[c0 + lane] = psi0;
@@ -1303,58 +1444,52 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             continue;
           }
         }
-        // ---- candidates: slot 0 = single device `lane`; slots 1..3 = windows
+        // ---- candidates: the single {lane} on its own lane; the window of size
+        // k = s + 2 starting at device i on lane i of slot s
         const uint32_t c0 = sv.c0;
-        const int nwin = (int)sv.nc - D;
-        const int wslots = (nwin + G - 1) / G;
+        int nk = 0;  // window sizes present: 2 .. nk + 1
+        for (int rem = (int)sv.nc - D; rem > 0; rem -= D - nk) ++nk;
         const float j0_single = a_imm + b_imm;
         double acc0 = 0.0;
-        int w_i[3], w_k[3];
-        float w_j0[3];
-        bool w_ok[3];
-        double w_acc[3];
+        float w_j0[3] = {0.0f, 0.0f, 0.0f};
+        bool w_ok[3] = {false, false, false};
+        double w_acc[3] = {0.0, 0.0, 0.0};
+        if (emits) {  // uniform
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            w_i[s] = 0; w_k[s] = 2; w_j0[s] = 0.0f; w_ok[s] = false; w_acc[s] = 0.0;
-            if (s >= wslots) continue;  // uniform
-            const int t = lane + s * G;
-            int i = 0, k = 2;
-            if (t < nwin) decode_window(t, D, i, k);
-            const float rk = fast_rcp((float)k);
-            float tmax = -inf_f();
+            for (int s = 0; s < 3; ++s) {
+                if (s >= nk) continue;  // uniform within the group
+                const int k = s + 2;
+                // maximum over devices i..i+k-1 (a lane whose source is past the group holds no window)
+                float y = a_imm + b_imm * (1.0f / (float)k);
+                float tmax = y;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int src = min(i + q, G - 1);
-                const float aq = __shfl(a_imm, src, G);
-                const float bq = __shfl(b_imm, src, G);
-                if (q < k) tmax = fmaxf(tmax, aq + bq * rk);
-            }
-            const uint64_t wm = ((1ull << k) - 1ull) << i;
-            const bool feasible = windows_on && (t < nwin) && ((feas_mask & wm) == wm);
-            float gat = inf_f();
-            if (feasible) {
-                for (int p = i; p < i + k; ++p) {
-                    float sum = 0.0f;
-                    for (int d = i; d < i + k; ++d)
-                        if (d != p) sum += a.beta[d * D + p] * sv.sigma * rk;
-                    gat = fminf(gat, sum);
+                for (int q = 1; q < k; ++q) {
+                    y = from_right<G>(y, lane);
+                    tmax = fmaxf(tmax, y);
                 }
+                const uint64_t wm = (1ull << k) - 1ull;
+                w_ok[s] = windows_on && lane <= D - k && ((feas_mask >> lane) & wm) == wm;
+                float gat = inf_f();
+                if (w_ok[s]) {
+#pragma unroll
+                    for (int p = 0; p < k; ++p) {
+                        float sum = 0.0f;
+#pragma unroll
+                        for (int d = 0; d < k; ++d)
+                            if (d != p)
+                                sum += (kTab ? btab[(lane + d) * bstr + lane + p] : a.beta[(lane + d) * D + lane + p]) * sv.sigma * (1.0f / (float)k);
+                        gat = fminf(gat, sum);
+                    }
+                }
+                w_j0[s] = tmax + lam_tr * gat;
             }
-            w_i[s] = i;
-            w_k[s] = k;
-            w_ok[s] = feasible;
-            w_j0[s] = tmax + lam_tr * gat;
         }
 
         // ---- horizon descendants, G at a time (a part of a heavy stage: its rows)
-        const int nparts = kSplit ? (int)(sb + plan.parts)[pos] : 1;
-        const uint32_t plen = kSplit && nparts > 1 ? reinterpret_cast<const uint32_t *>(sb + plan.plen)[pos] : 0u;
-        const uint32_t b_lo = sv.e0 + (uint32_t)part * plen;
-        const uint32_t b_hi = nparts > 1 ? min(sv.e1, b_lo + plen) : sv.e1;
         for (uint32_t base = b_lo; base < b_hi; base += G) {  // uniform; a part is whole G-row batches
             const int nb = stage_batch(base);
             int jj = 0;
-            if (UNI && wslots == 0) {  // singletons only: two descendants per iteration
+            if (UNI && nk == 0) {  // singletons only: two descendants per iteration
                 for (; jj + 1 < nb; jj += 2) {
                     float B0, N0, g0, B1, N1, g1;
                     bool c0c, c1c;
@@ -1382,48 +1517,77 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
                 entry_row(area[jj], Bd, inval, gh, child);
                 const float Pm = scan_min_up<G>(Bd, lane);
                 const float Qm = scan_min_down<G>(Bd, lane);
+                // a child of v with non-uniform beta: per candidate, the minimum
+                // over the devices outside it of B plus v's output moved there
+                // from the candidate's cheapest device.  The row of B goes
+                // through LDS, four devices at a time, against the candidate's row
+                // of the transfer table (+infinity inside the candidate).
+                const float mv_out = lam_tr * sv.sigma;
+                const bool moves = kTab && child && mv_out > 0.0f;  // uniform within the group; at 0 the minimum is the plain one
+                float far[4] = {inf_f(), inf_f(), inf_f(), inf_f()};
+                if constexpr (kTab) {
+                    if (moves) {
+                        float *brow = reinterpret_cast<float *>(sb + plan.brow) + (tid & ~(G - 1));
+                        brow[lane] = Bd;
+                        wave_sync();
+                        const float *crow[4];
+                        crow[0] = btab + dl * bstr;
+#pragma unroll
+                        for (int s = 0; s < 3; ++s)  // windows of size k start after the singles and the smaller sizes
+                            crow[s + 1] = s < nk ? btab + ((s + 1) * D - (s * (s + 1)) / 2 + min(lane, D - s - 2)) * bstr : crow[0];
+                        for (int d0 = 0; d0 < D; d0 += 4) {  // uniform; lanes past D hold +infinity
+                            const float4 bv = *reinterpret_cast<const float4 *>(brow + d0);
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) {
+                                if (s > nk) continue;  // uniform within the group
+                                const float4 tv = *reinterpret_cast<const float4 *>(crow[s] + d0);
+                                far[s] = fminf(fminf(far[s], bv.x + mv_out * tv.x), bv.y + mv_out * tv.y);
+                                far[s] = fminf(fminf(far[s], bv.z + mv_out * tv.z), bv.w + mv_out * tv.w);
+                            }
+                        }
+                    }
+                }
+                const float Lm = from_left<G>(Pm, lane);
+                float Rm = from_right<G>(Qm, lane);
                 {  // single device `lane`
-                    float excl = fminf(from_left<G>(Pm, lane), from_right<G>(Qm, lane));
+                    float excl = fminf(Lm, Rm);
                     if (UNI) {
                         excl += child ? t0 : 0.0f;
+                    } else if constexpr (kTab) {
+                        if (moves) excl = far[0];
                     } else if (child) {
-                        {
-                            excl = inf_f();
-                            for (int dd = 0; dd < D; ++dd) {  // uniform trip count
-                                const float bdd = __shfl(Bd, dd, G);
-                                if (dd != lane)
-                                    excl = fminf(excl, bdd + lam_tr * sv.sigma * a.beta[dl * D + dd]);
-                            }
+                        excl = inf_f();
+                        for (int dd = 0; dd < D; ++dd) {  // uniform trip count
+                            const float bdd = __shfl(Bd, dd, G);
+                            if (dd != lane)
+                                excl = fminf(excl, bdd + lam_tr * sv.sigma * a.beta[dl * D + dd]);
                         }
                     }
                     acc0 += (double)(gh * fminf(excl, inval));
                 }
+                float inside = inval;
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {  // windows
-                    if (s >= wslots) continue;  // uniform
-                    const int i = w_i[s], k = w_k[s];
-                    const float left = __shfl(Pm, max(i - 1, 0), G);
-                    const float right = __shfl(Qm, min(i + k, G - 1), G);
-                    float excl = fminf(i > 0 ? left : inf_f(), i + k < G ? right : inf_f());
-                    if (child) {
-                        if (UNI) {
-                            excl += t0;
-                        } else {
-                            excl = inf_f();
-                            for (int dd = 0; dd < D; ++dd) {  // uniform trip count
-                                const float bdd = __shfl(Bd, dd, G);
-                                if (dd >= i && dd < i + k) continue;
-                                float bmin = inf_f();
-                                for (int q = 0; q < k; ++q) bmin = fminf(bmin, a.beta[(i + q) * D + dd]);
-                                excl = fminf(excl, bdd + lam_tr * sv.sigma * bmin);
-                            }
+                for (int s = 0; s < 3; ++s) {  // windows {lane .. lane + s + 1}: one more device on the right each
+                    if (s >= nk) continue;  // uniform within the group
+                    const int k = s + 2;
+                    Rm = from_right<G>(Rm, lane);
+                    inside = fminf(inside, from_right<G>(inside, lane));
+                    float excl = fminf(Lm, Rm);
+                    if (UNI) {
+                        excl += child ? t0 : 0.0f;
+                    } else if constexpr (kTab) {
+                        if (moves) excl = far[s + 1];
+                    } else if (child) {
+                        excl = inf_f();
+                        const int i = min(lane, D - k);
+                        for (int dd = 0; dd < D; ++dd) {  // uniform trip count
+                            const float bdd = __shfl(Bd, dd, G);
+                            if (dd >= i && dd < i + k) continue;
+                            float bmin = inf_f();
+#pragma unroll
+                            for (int q = 0; q < k; ++q) bmin = fminf(bmin, a.beta[(i + q) * D + dd]);
+                            excl = fminf(excl, bdd + lam_tr * sv.sigma * bmin);
                         }
-                    }
-                    float inside = inf_f();
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float x = __shfl(inval, min(i + q, G - 1), G);
-                        if (q < k) inside = fminf(inside, x);
                     }
                     w_acc[s] += (double)(gh * fminf(excl, inside));
                 }
@@ -1445,14 +1609,61 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             for (int q = 0; q < nparts; ++q) acc0 += pool[(slot0 + q) * 64 + lane];
         }
 
-        // ---- emit scores
+        if (rows_only) {  // uniform over the block: the group leaves its sums in its own staging slots
+            double *sum = reinterpret_cast<double *>(area);
+            if (active) {
+                sum[lane] = acc0;
+#pragma unroll
+                for (int s = 0; s < 3; ++s) sum[(s + 1) * G + lane] = w_acc[s];
+            }
+            __syncthreads();
+            pass = 1;
+            continue;
+        }
+        if (oneshot)  // the stage's parts in row order
+            for (int q = 0; q < (int)sv.parts; ++q) {
+                const double *sum = reinterpret_cast<const double *>(reinterpret_cast<const Entry *>(L.entries) + ((int)sv.part0 + q) * G);
+                acc0 += sum[lane];
+#pragma unroll
+                for (int s = 0; s < 3; ++s) w_acc[s] += sum[(s + 1) * G + lane];
+            }
+
+        // ---- emit scores, and the top-k from the scores held here (the same float values)
         const float psi0 = feas_v ? (float)(-((double)j0_single + acc0)) : -inf_f();
         if (live) scores[c0 + lane] = psi0;
+        uint32_t off = c0 + (uint32_t)D;
+        float psiw[3] = {-inf_f(), -inf_f(), -inf_f()};
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
-            if (s >= wslots) continue;  // uniform
-            const int t = lane + s * G;
-            if (t < nwin) scores[c0 + D + t] = w_ok[s] ? (float)(-((double)w_j0[s] + w_acc[s])) : -inf_f();
+            if (s >= nk) continue;  // uniform within the group
+            const int k = s + 2;
+            psiw[s] = w_ok[s] ? (float)(-((double)w_j0[s] + w_acc[s])) : -inf_f();
+            if (lane <= D - k) scores[off + lane] = psiw[s];
+            off += (uint32_t)(D - k + 1);
+        }
+        if (a.topk > 0) {  // uniform over the launch
+            const int64_t f = (int64_t)f0 + si;
+            int32_t *ti = a.tk_idx + f * a.topk;
+            float *tv = a.tk_val + f * a.topk;
+            if (nk == 0) {  // uniform within the group
+                uint32_t sbits[1] = {live ? topk_bits(psi0) : 0u};
+                const uint32_t ci[1] = {(uint32_t)lane};
+                group_topk_at<G, 1>(sbits, ci, lane, a.topk, ti, tv);
+            } else {
+                uint32_t sbits[4], ci[4];
+                sbits[0] = live ? topk_bits(psi0) : 0u;
+                ci[0] = (uint32_t)lane;
+                uint32_t base_c = (uint32_t)D;
+#pragma unroll
+                for (int s = 0; s < 3; ++s) {
+                    const int k = s + 2;
+                    const bool has = s < nk && lane <= D - k;
+                    sbits[s + 1] = has ? topk_bits(psiw[s]) : 0u;
+                    ci[s + 1] = has ? base_c + (uint32_t)lane : 0xfffffff0u + (uint32_t)s;  // distinct, never picked
+                    base_c += s < nk ? (uint32_t)(D - k + 1) : 0u;
+                }
+                group_topk_at<G, 4>(sbits, ci, lane, a.topk, ti, tv);
+            }
         }
     }
 
@@ -1472,29 +1683,6 @@ __global__ __launch_bounds__(BLK) void k_score(ScoreLaunch a) {
             const int64_t f = (int64_t)f0 + i;
             lane_topk16(x, a.topk, a.tk_idx + f * a.topk, a.tk_val + f * a.topk);
         }
-    }
-
-    // ---- fused top-k: after the block's scoring, each group ranks a fixed
-    // share of its stages, re-reading the scores just written (outside the
-    // scoring loop, so it adds no register pressure there)
-    if (a.topk > 0 && !kSlots) {  // uniform over the block; the slot layout ranks in its loop
-        __syncthreads();  // stages were scored by whichever wave claimed them
-        constexpr int kRounds = 8;  // a slice holds at most eight rounds of groups
-        uint32_t c0[kRounds];
-        int C[kRounds];
-        int64_t f[kRounds];
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            const int pos = tid / G + r * kGroups;
-            c0[r] = 0; C[r] = 0; f[r] = -1;
-            if (pos < nF) {
-                const int si = (int)L.order[pos];
-                c0[r] = L.stages[si].c0;
-                C[r] = (int)L.stages[si].nc;
-                f[r] = (int64_t)f0 + si;
-            }
-        }
-        rank_stages<G, kRounds>(scores, c0, C, f, lane, a.topk, a.tk_idx, a.tk_val);
     }
 }
 
@@ -2532,7 +2720,12 @@ struct ScoreShape {
     bool slots, split;
     int block;
     size_t lds;
+    size_t lds2;  // of workgroups of kScoreBlock2 threads (8- to 32-lane groups)
 };
+
+// Threads per scoring workgroup where the launch would leave the chip idle
+// with kScoreBlock (8- to 32-lane groups): twice the lane groups per slice.
+constexpr int kScoreBlock2 = 512;
 
 // 16-lane groups with uniform beta and at most 32 models take the slot
 // layout; 64-lane groups take the first of (heavy-stage parts, 1024 threads),
@@ -2542,10 +2735,13 @@ static bool score_shape(int D, int K, int M, int slice, bool uni, ScoreShape &sh
     const int G = group_width(D);
     sh.slots = uni && G == 16 && M <= 32;
     sh.split = false;
+    sh.lds2 = 0;
     sh.block = score_block(G);
     if (G < 64) {
-        const int sb = G == 16 ? staging_bytes<16, score_block(16)>() : staging_bytes<8, score_block(8)>();
-        sh.lds = lds_plan(D, K, M, slice, sb, sh.slots, false).total;
+        const int sb = G == 16 ? staging_bytes<16, kScoreBlock>() : staging_bytes<8, kScoreBlock>();
+        sh.lds = lds_plan(D, K, M, slice, sb, sh.slots, false, uni, kScoreBlock).total;
+        const int sb2 = G == 16 ? staging_bytes<16, kScoreBlock2>() : staging_bytes<8, kScoreBlock2>();
+        sh.lds2 = lds_plan(D, K, M, slice, sb2, sh.slots, false, uni, kScoreBlock2).total;
         return sh.lds <= kLdsLimit;
     }
     const bool split[3] = {true, false, false};
@@ -2553,7 +2749,7 @@ static bool score_shape(int D, int K, int M, int slice, bool uni, ScoreShape &sh
     for (int c = 0; c < 3; ++c) {
         const int sb = block[c] == score_block(64) ? staging_bytes<64, score_block(64)>()
                                                    : staging_bytes<64, score_block(64) / 2>();
-        const size_t lds = lds_plan(D, K, M, slice, sb, false, split[c]).total;
+        const size_t lds = lds_plan(D, K, M, slice, sb, false, split[c], uni, block[c]).total;
         if (lds <= kLdsLimit) {
             sh.split = split[c];
             sh.block = block[c];
@@ -2625,23 +2821,43 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
         if (a.nsets == 0) return;
     }
     const int G = group_width(a.D);
-    const dim3 grid((unsigned)a.n_slices, (unsigned)a.nsets), block((unsigned)sh.block);
-    const size_t lds = sh.lds;
+    // Wide workgroups while one per instance is resident at once (two of 512
+    // threads per compute unit by registers, fewer where their LDS does not
+    // fit): fork-join-sized slices keep every group busy either way, small
+    // ones (eight stages on eight 32-lane groups) gain a second group per stage
+    // (333 layered instances on 24 devices with tiered links: 54 to 38 us with
+    // the rest of the one-shot path).  The rule reads nothing that differs
+    // between a plain and a planning state, or between a sweep and its single
+    // calls: which rows share a part decides the rounding of their sum.
+    const int64_t per_cu = std::min<int64_t>(2, (int64_t)(kLdsLimit / (sh.lds2 ? sh.lds2 : kLdsLimit + 1)));
+    const bool wide = G >= 8 && G <= 32 && a.B <= 256 * per_cu;
+    const dim3 grid((unsigned)a.n_slices, (unsigned)a.nsets), block((unsigned)(wide ? kScoreBlock2 : sh.block));
+    const size_t lds = wide ? sh.lds2 : sh.lds;
     bool var = a.topo != 0;
     for (int p = 0; p < a.nsets; ++p) var = var || a.ps[p].lam_m != 0.0f || a.ps[p].flags != 0;
-    constexpr int B0 = kScoreBlock, B64 = score_block(64);
+    constexpr int B0 = kScoreBlock, B2 = kScoreBlock2, B64 = score_block(64);
     switch (G) {
         case 4: hipLaunchKernelGGL((k_score<4, UNI, false, true, false, B0>), grid, block, lds, s, a); break;
-        case 8: hipLaunchKernelGGL((k_score<8, UNI, false, true, false, B0>), grid, block, lds, s, a); break;
+        case 8:
+            if (wide) hipLaunchKernelGGL((k_score<8, UNI, false, true, false, B2>), grid, block, lds, s, a);
+            else hipLaunchKernelGGL((k_score<8, UNI, false, true, false, B0>), grid, block, lds, s, a);
+            break;
         case 16:
             if (UNI && sh.slots) {
-                if (var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0>), grid, block, lds, s, a);
+                if (wide && var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B2>), grid, block, lds, s, a);
+                else if (wide) hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B2>), grid, block, lds, s, a);
+                else if (var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0>), grid, block, lds, s, a);
                 else hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B0>), grid, block, lds, s, a);
+            } else if (wide) {
+                hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B2>), grid, block, lds, s, a);
             } else {
                 hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B0>), grid, block, lds, s, a);
             }
             break;
-        case 32: hipLaunchKernelGGL((k_score<32, UNI, false, true, false, B0>), grid, block, lds, s, a); break;
+        case 32:
+            if (wide) hipLaunchKernelGGL((k_score<32, UNI, false, true, false, B2>), grid, block, lds, s, a);
+            else hipLaunchKernelGGL((k_score<32, UNI, false, true, false, B0>), grid, block, lds, s, a);
+            break;
         default:
             if (sh.split) hipLaunchKernelGGL((k_score<64, UNI, false, true, true, B64>), grid, block, lds, s, a);
             else if (sh.block == B64) hipLaunchKernelGGL((k_score<64, UNI, false, true, false, B64>), grid, block, lds, s, a);
