@@ -1024,6 +1024,8 @@ static fate_status_t topk_impl(const fate_state_h *state, const float *d_scores,
     a.nsets = n_sets;
     a.D = state->D;
     a.k = k;
+    a.singles = state->n_cand == state->n_frontier * (int64_t)state->D;  // every stage has at least D
+    a.vin = a.vout = 0;
     return fate::launch_topk(a, stream) == 0 ? FATE_OK : FATE_EHIP;
 }
 

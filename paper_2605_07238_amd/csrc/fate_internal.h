@@ -106,6 +106,8 @@ struct TopkLaunch {
     int64_t out_stride;       // its top-k at idx / val + p * out_stride
     int32_t nsets;
     int32_t D, k;
+    int32_t singles;    // every stage has exactly D candidates
+    int32_t vin, vout;  // float4 reads, four-word stores (set by the launcher)
 };
 
 // Commit-and-advance of a planning state (fate_commit.hip).
@@ -151,7 +153,7 @@ struct CommitLaunch {
 bool rows_kernel_fits(int D, int K, int M);
 
 // Whether scoring on this batch takes a row kernel (k_rows, k_rows4) for
-// parameter sets without a variant: single-device candidates only, uniform
+// parameter sets that sum over the levels: single-device candidates only, uniform
 // beta, hop levels, and tables that fit.  Its scoring slices then go unused,
 // and the packer and the commit leave them in instance order; otherwise they
 // follow the dispatch order (largest frontiers first).

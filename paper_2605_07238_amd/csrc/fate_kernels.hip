@@ -595,13 +595,12 @@ constexpr uint32_t kRankedInLoop = 0xffffffffu;
 // a list sorted by bits descending and displaces only strictly smaller
 // entries, so among equal scores the lower index ranks first.  The pick is
 // (index, score), or (-1, -inf) once the candidates run out.
-__device__ __forceinline__ void lane_topk16(const uint32_t (&x)[16], int k, int32_t *out_i, float *out_v) {
-    uint32_t t[kLaneTopk];
-    int32_t ix[kLaneTopk];
+template <int N>
+__device__ __forceinline__ void lane_rank(const uint32_t (&x)[N], uint32_t (&t)[kLaneTopk], int32_t (&ix)[kLaneTopk]) {
 #pragma unroll
     for (int r = 0; r < kLaneTopk; ++r) { t[r] = 0u; ix[r] = -1; }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
+    for (int j = 0; j < N; ++j) {
         const uint32_t c = x[j];
         bool gt[kLaneTopk];
 #pragma unroll
@@ -614,6 +613,11 @@ __device__ __forceinline__ void lane_topk16(const uint32_t (&x)[16], int k, int3
         t[0] = gt[0] ? c : t[0];
         ix[0] = gt[0] ? j : ix[0];
     }
+}
+__device__ __forceinline__ void lane_topk16(const uint32_t (&x)[16], int k, int32_t *out_i, float *out_v) {
+    uint32_t t[kLaneTopk];
+    int32_t ix[kLaneTopk];
+    lane_rank(x, t, ix);
 #pragma unroll
     for (int r = 0; r < kLaneTopk; ++r) {
         if (r < k) {
@@ -1715,9 +1719,60 @@ __global__ __launch_bounds__(kBlock) void k_topk(TopkLaunch a) {
     }
 }
 
+// Top-k of stages with exactly D <= ND <= 16 candidates each, k <= 4: one lane
+// per stage, which reads its scores as whole float4s where D == ND and they
+// are aligned (a.vin), and stores its picks as one word of each output where
+// k == 4 and those are (a.vout).  k_topk's groups spend a lane per candidate and
+// two reductions per pick; a lane that ranks alone spends its compares only.
+// Bound by memory: 1.6 M stages of 16 candidates (14 score sets of 1,024
+// fork-join instances), 156 MB, 91.5 us in k_topk, 26.1 us here (6.0 TB/s).
+// More devices or picks keep k_topk, whose groups hold what a lane cannot.
+template <int ND>
+__global__ __launch_bounds__(kBlock) void k_topk_lane(TopkLaunch a) {
+    const int64_t nF = a.dcounts ? (int64_t)a.dcounts[0] : a.nF;  // planning state: current frontier
+    const float *const scores = a.scores + (int64_t)blockIdx.y * a.score_stride;
+    const int64_t oo = (int64_t)blockIdx.y * a.out_stride;
+    const int D = a.D, k = a.k;
+    for (int64_t f = (int64_t)blockIdx.x * kBlock + threadIdx.x; f < nF; f += (int64_t)gridDim.x * kBlock) {
+        float x[ND];
+        if (a.vin) {  // uniform
+            const float4 *row = reinterpret_cast<const float4 *>(scores + f * ND);
+#pragma unroll
+            for (int q = 0; q < ND / 4; ++q) {
+                const float4 v = row[q];
+                x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < ND; ++q) x[q] = q < D ? scores[f * D + q] : -inf_f();
+        }
+        uint32_t bits[ND], t[kLaneTopk];
+        int32_t ix[kLaneTopk];
+#pragma unroll
+        for (int q = 0; q < ND; ++q) bits[q] = topk_bits(x[q]);
+        lane_rank(bits, t, ix);
+        float v[kLaneTopk];
+#pragma unroll
+        for (int r = 0; r < kLaneTopk; ++r) v[r] = t[r] != 0u ? order_bits_inv(t[r]) : -inf_f();
+        int32_t *oi = a.idx + oo + f * k;
+        float *ov = a.val + oo + f * k;
+        if (a.vout) {  // uniform
+            *reinterpret_cast<int4 *>(oi) = make_int4(ix[0], ix[1], ix[2], ix[3]);
+            *reinterpret_cast<float4 *>(ov) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < kLaneTopk; ++r)
+                if (r < k) {
+                    oi[r] = ix[r];
+                    ov[r] = v[r];
+                }
+        }
+    }
+}
+
 // ---- k_rows: one horizon row per lane ---------------------------------------
 // For frontiers whose stages have single-device candidates only, with a
-// uniform off-diagonal beta, D <= 16 and no scoring variant.  One workgroup
+// uniform off-diagonal beta, D <= 16, hop levels and their sum.  One workgroup
 // per instance: it stages the instance's tables in LDS once (prefix-group
 // table, per-(model, device) cost terms, and, per pair of models, the devices
 // where loading the first flips the residency of the second), then takes the
@@ -1854,7 +1909,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             const int j = m * D + d;
             const float ks = ps.lam_s * a.ksw[j];
             const bool res = bit(a.resident[(int64_t)b * D + d], m);
-            const float swo = res ? 0.0f : ks;
+            const float swo = res ? 0.0f - ps.lam_m : ks;  // the same-model weight beside the switch time
             sw0 = a.exec[j] + swo;
             CostS c;
             c.sw0 = sw0;
@@ -1867,7 +1922,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             // sign of the change a flip of the residency makes: up where m is
             // resident now (evicted), down where it is not (loaded)
             if (!bit(a.fits[m], d)) sw0 = inf_f();
-            sks = res ? ks : -ks;
+            sks = res ? ks + ps.lam_m : -(ks + ps.lam_m);
         }
         rtab[m * CS + 2 * d] = sw0;  // devices past D: never feasible
         rtab[m * CS + 2 * d + 1] = sks;
@@ -2364,11 +2419,11 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             const int j = m * D + d;
             const float ks = ps.lam_s * a.ksw[j];
             const bool res = bit(a.resident[(int64_t)b * D + d], m);
-            sw0 = a.exec[j] + (res ? 0.0f : ks);
+            sw0 = a.exec[j] + (res ? 0.0f - ps.lam_m : ks);  // the same-model weight beside the switch time
             // +infinity where the model does not fit; the magnitude signed by
             // the change a flip of the residency makes (up where resident now)
             if (!bit(a.fits[m], d)) sw0 = inf_f();
-            sks = res ? ks : -ks;
+            sks = res ? ks + ps.lam_m : -(ks + ps.lam_m);
         }
         rtab[m * CS + 2 * d] = sw0;  // devices past D: never feasible
         rtab[m * CS + 2 * d + 1] = sks;
@@ -2669,8 +2724,10 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
                 }
             }
             // the switch term where m(v) is not resident (the row table's
-            // magnitude is negative there)
-            const float swo = bit(rho[dl], s.model) ? 0.0f : -rtab[s.model * CS + 2 * dl + 1];
+            // magnitude is negative there, and holds the same-model weight too)
+            const float swo = bit(rho[dl], s.model) ? 0.0f - ps.lam_m
+                              : ps.lam_m == 0.0f    ? -rtab[s.model * CS + 2 * dl + 1]
+                                                    : ps.lam_s * a.ksw[s.model * D + dl];
             const float ex = a.exec[s.model * D + dl];
             const float pf_v = ((s.pfm >> dl) & 1ull) ? ps.kpf * s.tokens : 0.0f;
             const float colo = s.npar ? cnt * fast_rcp((float)s.npar) : 0.0f;
@@ -2770,7 +2827,7 @@ constexpr int kRowsBlock = 256;
 constexpr int kRows4Block = 1024;
 
 // The row kernels take frontiers with single-device candidates only, uniform
-// beta, hop levels and parameter sets without a scoring variant: k_rows up
+// beta, hop levels and parameter sets that sum over the levels: k_rows up
 // to 16 devices and 32 models, k_rows4 up to 64 devices and 64 models, when
 // their LDS fits.
 bool rows_kernel_fits(int D, int K, int M) {
@@ -2807,12 +2864,15 @@ template <bool UNI>
 static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStream_t s) {
     ScoreLaunch a = a0;
     if (UNI && rows_fit(a0)) {
-        // each parameter set goes where a launch of that set alone would go:
-        // sets without a variant to k_rows, the others below
+        // each parameter set goes where a launch of that set alone would go: the
+        // row kernels take all but the mean per level (its weights are per
+        // descendant entry), which goes below.  There are no windows to turn
+        // off here, and the same-model weight is part of the switch table: on
+        // 1,024 fork-join instances such a set took 104 us in k_score, 27 in k_rows
         ScoreLaunch r = a0;
         r.nsets = a.nsets = 0;
         for (int p = 0; p < a0.nsets; ++p) {
-            ScoreLaunch &x = (a0.ps[p].lam_m != 0.0f || a0.ps[p].flags != 0) ? a : r;
+            ScoreLaunch &x = (a0.ps[p].flags & FATE_MEAN_PER_LEVEL) != 0 ? a : r;
             x.ps[x.nsets] = a0.ps[p];
             x.set_of[x.nsets] = a0.set_of[p];
             ++x.nsets;
@@ -2880,6 +2940,20 @@ int launch_topk(const TopkLaunch &a, void *stream) {
     const int64_t per_block = (int64_t)(kBlock / G) * kTopkRounds;
     const int64_t blocks = std::min((a.nF + per_block - 1) / per_block, kTopkMaxBlocks);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (a.singles && a.D <= 16 && a.k <= kLaneTopk) {
+        TopkLaunch l = a;
+        const int nd = a.D <= 4 ? 4 : a.D <= 8 ? 8 : 16;
+        auto at16 = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
+        l.vin = a.D == nd && at16(a.scores) && (a.nsets == 1 || a.score_stride % 4 == 0);
+        l.vout = a.k == 4 && at16(a.idx) && at16(a.val);  // sets are whole multiples of k apart
+        const dim3 lgrid((unsigned)std::min((a.nF + kBlock - 1) / kBlock, kTopkMaxBlocks), (unsigned)a.nsets);
+        switch (nd) {
+            case 4: hipLaunchKernelGGL(k_topk_lane<4>, lgrid, dim3(kBlock), 0, s, l); break;
+            case 8: hipLaunchKernelGGL(k_topk_lane<8>, lgrid, dim3(kBlock), 0, s, l); break;
+            default: hipLaunchKernelGGL(k_topk_lane<16>, lgrid, dim3(kBlock), 0, s, l); break;
+        }
+        return (int)hipGetLastError();
+    }
     const dim3 grid((unsigned)blocks, (unsigned)a.nsets);
     switch (G) {
         case 4: hipLaunchKernelGGL(k_topk<4>, grid, dim3(kBlock), 0, s, a); break;

@@ -114,3 +114,45 @@ def test_rows4_topk(k):
     w = _rows_workload(34, D=64, M=6, K=4, n=50)
     print("[rows4] k", k, flush=True)
     check_against_oracle(w, run_gpu(w, k=k), k=k)
+
+
+@pytest.mark.parametrize("D,M", [(4, 3), (7, 5), (16, 12), (24, 6), (64, 9)])
+def test_rows_variants(D, M):
+    """The same-model weight and windows switched off on frontiers without
+    windows stay in the row kernels."""
+    w = _rows_workload(60 + D, D=D, M=M, K=4, n=60, p_edge=0.08)
+    for p in (dict(lam_m=0.3), dict(lam_m=2.0, lam_s=0.5, no_windows=1), dict(no_windows=1)):
+        print("[rows] variants", D, p, flush=True)
+        check_against_oracle(w, run_gpu(w, k=4, params=p), k=4, params=p)
+
+
+@pytest.mark.parametrize("D", [1, 3, 4, 6, 8, 13, 16])
+@pytest.mark.parametrize("k", [1, 3, 4])
+def test_lane_topk(D, k):
+    """fate_topk on frontiers of exactly D candidates a stage, aligned or not,
+    against the rule (score descending, index ascending), with ties, padding
+    and unaligned scores, outputs and strides."""
+    import torch
+    from paper_2605_07238_amd import fate, parity
+    w = _rows_workload(80 + D, B=5, D=D, M=3, K=2, n=300, p_edge=0.005)
+    print("[rows] lane top-k", D, k, flush=True)
+    pk = fate.fate_pack_dags(w)
+    st = fate.fate_pack_state(pk, w)
+    F, C = st.n_frontier, st.n_cand
+    assert C == F * D and F > 256
+    rng = np.random.default_rng(D)
+    for shift in (0, 1):
+        x = rng.integers(-3, 4, (3, C + 5)).astype(np.float32) * np.float32(0.5)
+        x[rng.random(x.shape) < 0.2] = -np.inf
+        buf = torch.zeros(x.size + 1, device="cuda")
+        scores = buf[shift:shift + x.size].view(x.shape)
+        scores.copy_(torch.from_numpy(x))
+        out_i = torch.zeros(3 * F * k + 1, dtype=torch.int32, device="cuda")[shift:shift + 3 * F * k].view(3, F, k)
+        out_v = torch.zeros(3 * F * k + 1, device="cuda")[shift:shift + 3 * F * k].view(3, F, k)
+        fate.fate_topk_sweep(st, scores, k, idx=out_i, val=out_v)
+        off = np.arange(F + 1, dtype=np.int64) * D
+        for p in range(3):
+            want = parity.topk_of_scores(x[p, :C], off, k)
+            assert np.array_equal(out_i[p].cpu().numpy(), want)
+            vals = np.where(want >= 0, x[p][np.minimum(off[:-1, None] + np.maximum(want, 0), C - 1)], -np.inf)
+            assert np.array_equal(out_v[p].cpu().numpy(), vals.astype(np.float32))
