@@ -298,7 +298,9 @@ fate_status_t fate_pack_state_size(const fate_dags_t *packed, const fate_dag_bat
 
 /* fate_pack_state: validate, build the frontier list (ordered by instance,
  * then stage id) and candidate offsets, copy state and frontier to d_buf on
- * `stream` and synchronise.  Errors: as the size query, ESIZE, EHIP. */
+ * `stream`, gather the completed-parent lists there from the packed DAGs (on
+ * the host when those are not in the memory of d_buf's GPU) and synchronise.
+ * Errors: as the size query, ESIZE, EHIP. */
 fate_status_t fate_pack_state(const fate_dags_t *packed, const fate_dag_batch_t *dags,
                               const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                               void *stream, fate_state_h *out);

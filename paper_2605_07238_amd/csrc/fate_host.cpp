@@ -12,6 +12,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -340,8 +341,84 @@ struct StatePlan {
     int64_t nF = 0, nC = 0, nS = 0;
 };
 
-fate_status_t plan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const fate_state_t *st,
-                         int max_shard, StatePlan *p) {
+// One instance of the state: its frontier (appended to `front` when given),
+// their candidates, and the first error in stage order (the counts then end
+// before the stage at fault).
+struct InstScan {
+    uint32_t nf = 0;
+    int64_t nc = 0;
+    fate_status_t err = FATE_OK;
+};
+
+InstScan scan_instance(const fate_dag_batch_t *g, const fate_state_t *st, int D, int max_shard, int b,
+                       std::vector<uint32_t> *front) {
+    InstScan r;
+    const uint64_t dm = dev_mask(D);
+    const int64_t base = g->stage_off[b];
+    const int64_t n = g->stage_off[b + 1] - base;
+    for (int64_t v = 0; v < n; ++v) {
+        const int64_t s = base + v;
+        const uint8_t status = st->status[s];
+        const uint64_t hold = st->holders[s];
+        if (status > FATE_COMMITTED) r.err = FATE_EINVAL;
+        else if (hold & ~dm) r.err = FATE_ESTATE;
+        else if ((status == FATE_COMPLETED) != (hold != 0)) r.err = FATE_ESTATE;
+        if (r.err != FATE_OK) return r;
+        bool parents_done = true;
+        for (int64_t q = g->par_off[s]; q < g->par_off[s + 1]; ++q) {
+            const int64_t u = g->par_idx[q];
+            if (u < 0 || u >= v) {
+                r.err = FATE_ECYCLE;
+                return r;
+            }
+            parents_done &= st->status[base + u] == FATE_COMPLETED;
+        }
+        if ((status == FATE_COMPLETED || status == FATE_RUNNING) && !parents_done) {
+            r.err = FATE_ESTATE;
+            return r;
+        }
+        if (status == FATE_PENDING && parents_done) {
+            if (front) front->push_back((uint32_t)s);
+            ++r.nf;
+            r.nc += candidates_of(shard_cap(g->shard_max[s], max_shard, D), D);
+        }
+    }
+    return r;
+}
+
+// Stages per thread that are worth starting one for (about 0.2 ms of scanning
+// against some 20 us).
+constexpr int64_t kScanStages = 32768;
+
+// fn(t, first, end) for contiguous ranges of the instances with about equal
+// numbers of stages, one range per thread (the last on the caller's; a range
+// whose thread cannot be started too).
+template <class F>
+void instance_ranges(const fate_dag_batch_t *g, int64_t N, F &&fn) {
+    const int T = (int)std::max<int64_t>(1, std::min<int64_t>(fate_host::worker_count(), N / kScanStages));
+    std::vector<std::thread> ts;
+    int first = 0;
+    for (int t = 0; t < T; ++t) {
+        const int64_t upto = N * (t + 1) / T;
+        const int end = t + 1 == T ? g->B : (int)(std::lower_bound(g->stage_off + first, g->stage_off + g->B, upto) - g->stage_off);
+        bool started = false;
+        if (t + 1 < T) {
+            try {
+                ts.emplace_back([&fn, t, first, end] { fn(t, first, end); });
+                started = true;
+            } catch (const std::system_error &) {
+            }
+        }
+        if (!started) fn(t, first, end);
+        first = end;
+    }
+    for (auto &t : ts) t.join();
+}
+
+// Validate the state and count its frontier and candidates per instance;
+// fronts[t] receives the frontier stages of thread t's instances, in order.
+fate_status_t scan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const fate_state_t *st, int max_shard,
+                         std::vector<InstScan> *scan, std::vector<std::vector<uint32_t>> *fronts) {
     if (!pk || !g || !st) return FATE_EINVAL;
     if (max_shard < 1 || max_shard > FATE_MAX_SHARD) return FATE_ERANGE;
     if (st->K < 0 || st->K > FATE_MAX_PREFIX_SLOTS) return FATE_ERANGE;
@@ -354,48 +431,69 @@ fate_status_t plan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const
     if (B > 0 && K > 0 && !st->prefix_cache) return FATE_EINVAL;
     if (N > 0 && g->par_off[N] != pk->E) return FATE_ESTATE;
     const uint64_t mm = pk->M >= 64 ? ~0ull : ((1ull << pk->M) - 1ull);
-    const uint64_t dm = dev_mask(D);
     for (int64_t i = 0; i < (int64_t)B * D; ++i) {
         if (st->resident[i] & ~mm) return FATE_EINVAL;
         if (!std::isfinite(st->tau_free[i])) return FATE_EINVAL;
     }
     for (int b = 0; b < B; ++b)
         if (!std::isfinite(st->t_now[b])) return FATE_EINVAL;
-    p->cand_off.clear();
-    p->frontier.clear();
-    p->slices.clear();
-    p->fr_off.assign(B + 1, 0);
-    const int64_t slice = fate::slice_len(D);
+    scan->assign(B, InstScan());
+    if (fronts) fronts->assign(fate_host::worker_count(), {});
+    instance_ranges(g, N, [&](int t, int first, int end) {
+        std::vector<uint32_t> *front = fronts ? &(*fronts)[t] : nullptr;
+        for (int b = first; b < end; ++b) {
+            const InstScan r = scan_instance(g, st, D, max_shard, b, front);
+            (*scan)[b] = r;
+            if (r.err != FATE_OK) break;  // the first error of the batch is in this instance or an earlier one
+        }
+    });
+    // the first error in (instance, stage) order, the candidate total among them
     int64_t nc = 0;
     for (int b = 0; b < B; ++b) {
-        const int64_t base = g->stage_off[b];
-        const int64_t n = g->stage_off[b + 1] - base;
-        const int64_t first = (int64_t)p->frontier.size() / 2;
-        p->fr_off[b] = (uint32_t)first;
-        for (int64_t v = 0; v < n; ++v) {
-            const int64_t s = base + v;
-            const uint8_t status = st->status[s];
-            const uint64_t hold = st->holders[s];
-            if (status > FATE_COMMITTED) return FATE_EINVAL;
-            if (hold & ~dm) return FATE_ESTATE;
-            if ((status == FATE_COMPLETED) != (hold != 0)) return FATE_ESTATE;
-            bool parents_done = true;
-            for (int64_t q = g->par_off[s]; q < g->par_off[s + 1]; ++q) {
-                const int64_t u = g->par_idx[q];
-                if (u < 0 || u >= v) return FATE_ECYCLE;
-                if (st->status[base + u] != FATE_COMPLETED) parents_done = false;
-            }
-            if ((status == FATE_COMPLETED || status == FATE_RUNNING) && !parents_done) return FATE_ESTATE;
-            if (status == FATE_PENDING && parents_done) {
-                p->frontier.push_back((uint32_t)s);
-                p->frontier.push_back((uint32_t)b);
-                p->cand_off.push_back((uint32_t)nc);
-                nc += candidates_of(shard_cap(g->shard_max[s], max_shard, D), D);
-                if (nc >= (int64_t(1) << 32)) return FATE_ERANGE;
-            }
-        }
+        nc += (*scan)[b].nc;
+        if (nc >= (int64_t(1) << 32)) return FATE_ERANGE;
+        if ((*scan)[b].err != FATE_OK) return (*scan)[b].err;
     }
-    p->fr_off[B] = (uint32_t)(p->frontier.size() / 2);
+    return FATE_OK;
+}
+
+// Slices of the batch: stages of each instance cut into the scoring slices.
+int64_t slices_of(const std::vector<InstScan> &scan, int64_t slice) {
+    int64_t n = 0;
+    for (const InstScan &r : scan) n += ((int64_t)r.nf + slice - 1) / slice;
+    return n;
+}
+
+// lists: also gather the completed-parent lists (the device packer leaves
+// them to a kernel, which reads the holders it has just copied).
+fate_status_t plan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const fate_state_t *st,
+                         int max_shard, bool lists, StatePlan *p) {
+    std::vector<InstScan> scan;
+    std::vector<std::vector<uint32_t>> fronts;
+    fate_status_t err = scan_state(pk, g, st, max_shard, &scan, &fronts);
+    if (err != FATE_OK) return err;
+    const int B = g->B, D = pk->D, K = st->K;
+    const int64_t N = pk->N;
+    const int64_t slice = fate::slice_len(D);
+    p->slices.clear();
+    p->fr_off.assign(B + 1, 0);
+    for (int b = 0; b < B; ++b) p->fr_off[b + 1] = p->fr_off[b] + scan[b].nf;
+    p->nF = p->fr_off[B];
+    p->frontier.resize(2 * (size_t)p->nF);
+    p->cand_off.resize((size_t)p->nF + 1);
+    int64_t nc = 0, f = 0;
+    int fb = 0;
+    for (const std::vector<uint32_t> &front : fronts)
+        for (uint32_t s : front) {
+            while (f >= (int64_t)p->fr_off[fb + 1]) ++fb;
+            p->frontier[2 * f] = s;
+            p->frontier[2 * f + 1] = (uint32_t)fb;
+            p->cand_off[f] = (uint32_t)nc;
+            nc += candidates_of(shard_cap(g->shard_max[s], max_shard, D), D);
+            ++f;
+        }
+    p->cand_off[f] = (uint32_t)nc;
+    p->nC = nc;
     // per-instance launches take the largest frontiers first, so that the
     // last workgroups to start are short ones; the scoring slices follow the
     // same order where the general scoring kernel uses them
@@ -423,7 +521,12 @@ fate_status_t plan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const
     // completed parents of every pending stage (only pending stages are
     // scored, in the frontier or in a horizon), with their holders and
     // sizes, in the first of the stage's parent slots
-    p->done_n.assign(N, 0);
+    p->done_n.resize(N);
+    if (!lists) {  // which stages get a list
+        for (int64_t s = 0; s < N; ++s) p->done_n[s] = st->status[s] == FATE_PENDING ? 1u : 0u;
+        return FATE_OK;
+    }
+    std::fill(p->done_n.begin(), p->done_n.end(), 0u);
     fate::DoneParent zero;
     zero.holders = 0;
     zero.sigma = 0.0f;
@@ -444,9 +547,6 @@ fate_status_t plan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const
             p->done_n[s] = k;
         }
     }
-    p->cand_off.push_back((uint32_t)nc);
-    p->nF = (int64_t)p->frontier.size() / 2;
-    p->nC = nc;
     return FATE_OK;
 }
 
@@ -555,7 +655,7 @@ void fill_state_handle(const fate_dags_t *pk, const fate_state_t *st, int max_sh
     out->cand_off = reinterpret_cast<const uint32_t *>(base + L.cand_off);
     out->n_slices = p.nS;
     out->slices = reinterpret_cast<const uint32_t *>(base + L.slices);
-    out->n_done_edges = (int64_t)p.done.size();
+    out->n_done_edges = pk->E;
     out->done_n = reinterpret_cast<const uint32_t *>(base + L.done_n);
     out->done = base + L.done;
     out->fr_off = reinterpret_cast<const uint32_t *>(base + L.fr_off);
@@ -579,6 +679,81 @@ fate_status_t copy_to_device(void *d_buf, const void *h, size_t bytes, void *str
     if (hipMemcpyAsync(d_buf, h, bytes, hipMemcpyHostToDevice, s) != hipSuccess) return FATE_EHIP;
     if (hipStreamSynchronize(s) != hipSuccess) return FATE_EHIP;
     return FATE_OK;
+}
+
+// The state image in device memory: the caller's arrays are copied as they
+// are, the frontier's sections from the plan, and the completed-parent lists
+// (most of the image) and a planning state's finish times are built by a
+// kernel from the holders and the packed records.  Everything between and
+// past the sections' contents is zero.
+fate_status_t write_state_device(const fate_dags_t *pk, const fate_state_t *st, const StatePlan &p,
+                                 const StateLayout &L, uint8_t *d, void *stream) {
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const int B = pk->B, D = pk->D, K = st->K;
+    const bool advance = L.counts > L.status;
+    bool ok = true;
+    auto zero = [&](size_t from, size_t to) {
+        if (to > from) ok = ok && hipMemsetAsync(d + from, 0, to - from, s) == hipSuccess;
+    };
+    auto copy = [&](size_t at, const void *src, size_t n) {
+        if (n) ok = ok && hipMemcpyAsync(d + at, src, n, hipMemcpyHostToDevice, s) == hipSuccess;
+    };
+    const uint32_t counts[4] = {(uint32_t)p.nF, (uint32_t)p.nC, (uint32_t)p.nS, 0u};
+    zero(0, L.done);  // the kernel writes every list slot
+    zero(L.done + sizeof(fate::DoneParent) * (size_t)pk->E, L.total);
+    copy(L.resident, st->resident, sizeof(uint64_t) * B * D);
+    copy(L.pcache, st->prefix_cache, sizeof(uint64_t) * (size_t)B * D * K);
+    copy(L.holders, st->holders, sizeof(uint64_t) * pk->N);
+    copy(L.tau, st->tau_free, sizeof(float) * B * D);
+    copy(L.tnow, st->t_now, sizeof(float) * B);
+    copy(L.frontier, p.frontier.data(), sizeof(uint32_t) * p.frontier.size());
+    copy(L.cand_off, p.cand_off.data(), sizeof(uint32_t) * p.cand_off.size());
+    copy(L.slices, p.slices.data(), sizeof(uint32_t) * p.slices.size());
+    copy(L.done_n, p.done_n.data(), sizeof(uint32_t) * p.done_n.size());
+    copy(L.fr_off, p.fr_off.data(), sizeof(uint32_t) * p.fr_off.size());
+    copy(L.order, p.order.data(), sizeof(uint32_t) * p.order.size());
+    if (advance) {
+        copy(L.status, st->status, (size_t)pk->N);
+        copy(L.counts, counts, sizeof(counts));
+    }
+    fate::ListsLaunch a;
+    a.rec = static_cast<const StageRec *>(pk->records);
+    a.par_idx = pk->par_idx;
+    a.stage_off = pk->stage_off;
+    a.holders = reinterpret_cast<const uint64_t *>(d + L.holders);
+    a.tnow = reinterpret_cast<const float *>(d + L.tnow);
+    a.done_n = reinterpret_cast<uint32_t *>(d + L.done_n);
+    a.done = reinterpret_cast<fate::DoneParent *>(d + L.done);
+    a.finish = advance ? reinterpret_cast<float *>(d + L.finish) : nullptr;
+    a.B = B;
+    a.max_stages = pk->max_stages;
+    ok = ok && fate::launch_lists(a, stream) == 0;
+    // also after a failure: nothing may still read the caller's arrays or the plan
+    ok = hipStreamSynchronize(s) == hipSuccess && ok;
+    return ok ? FATE_OK : FATE_EHIP;
+}
+
+// Whether the packed DAGs are in the memory of the GPU that holds d_buf, so
+// that a kernel may read them there (a handle laid out in host memory is
+// packed on the host).
+bool on_same_gpu(const fate_dags_t *pk, const void *d_buf) {
+    hipPointerAttribute_t x, y;
+    if (pk->N == 0) return false;
+    if (hipPointerGetAttributes(&x, pk->records) != hipSuccess || hipPointerGetAttributes(&y, d_buf) != hipSuccess) {
+        (void)hipGetLastError();  // host memory that HIP does not know
+        return false;
+    }
+    return x.type == hipMemoryTypeDevice && y.type == hipMemoryTypeDevice && x.device == y.device;
+}
+
+// A packed state's image: sections and kernel, or (lists) the host's image
+// copied whole.
+fate_status_t pack_state_image(const fate_dags_t *pk, const fate_dag_batch_t *g, const fate_state_t *st,
+                               const StatePlan &p, const StateLayout &L, bool lists, void *d_buf, void *stream) {
+    if (!lists) return write_state_device(pk, st, p, L, static_cast<uint8_t *>(d_buf), stream);
+    std::vector<uint8_t> img(L.total, 0);
+    write_state_image(pk, g, st, p, L, img.data());
+    return copy_to_device(d_buf, img.data(), L.total, stream);
 }
 
 bool params_ok(const fate_params_t *p) {
@@ -692,24 +867,18 @@ fate_status_t fate_pack_state_size(const fate_dags_t *packed, const fate_dag_bat
                                    const fate_state_t *state, int32_t max_shard, size_t *bytes,
                                    int64_t *n_frontier, int64_t *n_cand) {
     if (!bytes) return FATE_EINVAL;
-    StatePlan p;
-    fate_status_t st = plan_state(packed, dags, state, max_shard, &p);
+    std::vector<InstScan> scan;
+    fate_status_t st = scan_state(packed, dags, state, max_shard, &scan, nullptr);
     if (st != FATE_OK) return st;
-    *bytes = state_layout(packed->B, packed->D, state->K, packed->N, p.nF, p.nS, packed->E).total;
-    if (n_frontier) *n_frontier = p.nF;
-    if (n_cand) *n_cand = p.nC;
-    return FATE_OK;
-}
-
-static fate_status_t build_state(const fate_dags_t *packed, const fate_dag_batch_t *dags,
-                                 const fate_state_t *state, int32_t max_shard, size_t bytes,
-                                 std::vector<uint8_t> &img, StatePlan &p, StateLayout &L) {
-    fate_status_t st = plan_state(packed, dags, state, max_shard, &p);
-    if (st != FATE_OK) return st;
-    L = state_layout(packed->B, packed->D, state->K, packed->N, p.nF, p.nS, packed->E);
-    if (bytes < L.total) return FATE_ESIZE;
-    img.assign(L.total, 0);
-    write_state_image(packed, dags, state, p, L, img.data());
+    int64_t nF = 0, nC = 0;
+    for (const InstScan &r : scan) {
+        nF += r.nf;
+        nC += r.nc;
+    }
+    *bytes = state_layout(packed->B, packed->D, state->K, packed->N, nF, slices_of(scan, fate::slice_len(packed->D)),
+                          packed->E).total;
+    if (n_frontier) *n_frontier = nF;
+    if (n_cand) *n_cand = nC;
     return FATE_OK;
 }
 
@@ -717,12 +886,13 @@ fate_status_t fate_layout_state(const fate_dags_t *packed, const fate_dag_batch_
                                 const fate_state_t *state, int32_t max_shard, void *h_buf, size_t bytes,
                                 fate_state_h *out) {
     if (!h_buf || !out) return FATE_EINVAL;
-    std::vector<uint8_t> img;
     StatePlan p;
-    StateLayout L;
-    fate_status_t st = build_state(packed, dags, state, max_shard, bytes, img, p, L);
+    fate_status_t st = plan_state(packed, dags, state, max_shard, true, &p);
     if (st != FATE_OK) return st;
-    copy_bytes(h_buf, img.data(), L.total);
+    const StateLayout L = state_layout(packed->B, packed->D, state->K, packed->N, p.nF, p.nS, packed->E);
+    if (bytes < L.total) return FATE_ESIZE;
+    if (L.total) std::memset(h_buf, 0, L.total);
+    write_state_image(packed, dags, state, p, L, static_cast<uint8_t *>(h_buf));
     fill_state_handle(packed, state, max_shard, p, L, static_cast<uint8_t *>(h_buf), bytes, out);
     return FATE_OK;
 }
@@ -731,12 +901,13 @@ fate_status_t fate_pack_state(const fate_dags_t *packed, const fate_dag_batch_t 
                               const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                               void *stream, fate_state_h *out) {
     if (!d_buf || !out) return FATE_EINVAL;
-    std::vector<uint8_t> img;
+    const bool lists = !packed || !on_same_gpu(packed, d_buf);
     StatePlan p;
-    StateLayout L;
-    fate_status_t st = build_state(packed, dags, state, max_shard, bytes, img, p, L);
+    fate_status_t st = plan_state(packed, dags, state, max_shard, lists, &p);
     if (st != FATE_OK) return st;
-    st = copy_to_device(d_buf, img.data(), L.total, stream);
+    const StateLayout L = state_layout(packed->B, packed->D, state->K, packed->N, p.nF, p.nS, packed->E);
+    if (bytes < L.total) return FATE_ESIZE;
+    st = pack_state_image(packed, dags, state, p, L, lists, d_buf, stream);
     if (st != FATE_OK) return st;
     fill_state_handle(packed, state, max_shard, p, L, static_cast<uint8_t *>(d_buf), bytes, out);
     return FATE_OK;
@@ -745,8 +916,8 @@ fate_status_t fate_pack_state(const fate_dags_t *packed, const fate_dag_batch_t 
 fate_status_t fate_pack_state_advance_size(const fate_dags_t *packed, const fate_dag_batch_t *dags,
                                            const fate_state_t *state, int32_t max_shard, size_t *bytes) {
     if (!bytes) return FATE_EINVAL;
-    StatePlan p;
-    fate_status_t st = plan_state(packed, dags, state, max_shard, &p);
+    std::vector<InstScan> scan;
+    fate_status_t st = scan_state(packed, dags, state, max_shard, &scan, nullptr);
     if (st != FATE_OK) return st;
     AdvanceCaps c;
     st = advance_caps(packed, dags, state, max_shard, &c);
@@ -759,17 +930,16 @@ fate_status_t fate_pack_state_advance(const fate_dags_t *packed, const fate_dag_
                                       const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                                       void *stream, fate_state_h *out) {
     if (!d_buf || !out) return FATE_EINVAL;
+    const bool lists = !packed || !on_same_gpu(packed, d_buf);
     StatePlan p;
-    fate_status_t st = plan_state(packed, dags, state, max_shard, &p);
+    fate_status_t st = plan_state(packed, dags, state, max_shard, lists, &p);
     if (st != FATE_OK) return st;
     AdvanceCaps c;
     st = advance_caps(packed, dags, state, max_shard, &c);
     if (st != FATE_OK) return st;
     const StateLayout L = state_layout(packed->B, packed->D, state->K, packed->N, c.nF, c.nS, c.nDone, true);
     if (bytes < L.total) return FATE_ESIZE;
-    std::vector<uint8_t> img(L.total, 0);
-    write_state_image(packed, dags, state, p, L, img.data());
-    st = copy_to_device(d_buf, img.data(), L.total, stream);
+    st = pack_state_image(packed, dags, state, p, L, lists, d_buf, stream);
     if (st != FATE_OK) return st;
     fill_state_handle(packed, state, max_shard, p, L, static_cast<uint8_t *>(d_buf), bytes, out);
     fill_advance_handle(c, L, static_cast<uint8_t *>(d_buf), out);

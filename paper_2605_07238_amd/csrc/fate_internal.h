@@ -230,6 +230,22 @@ bool score_fits(int D, int K, int M, int beta_uniform);
 int launch_topk(const TopkLaunch &a, void *stream);
 int launch_commit(const CommitLaunch &a, void *stream);  // fate_commit.hip
 
+// Completed-parent lists of a state being packed (fate_commit.hip): done_n
+// comes in as 1 for the stages that get a list (the pending ones), else 0.
+struct ListsLaunch {
+    const StageRec *rec;
+    const uint32_t *par_idx;
+    const int64_t *stage_off;
+    const uint64_t *holders;
+    const float *tnow;
+    uint32_t *done_n;
+    DoneParent *done;
+    float *finish;  // planning state: planned finish of the completed stages, or null
+    int32_t B;
+    int64_t max_stages;
+};
+int launch_lists(const ListsLaunch &a, void *stream);
+
 // Commit-and-advance behind both entry points (fate_host.cpp): validation,
 // then the three launches with the workspace d_ws of ws_bytes.  commit_check
 // runs the validation alone and returns the workspace bytes needed.

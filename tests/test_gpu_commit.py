@@ -406,3 +406,28 @@ def test_commit_inputs_ready_scenario():
         assert got["tau_free"].reshape(-1).tolist() == step["tau"], got["tau_free"]
         done = got["status"] == 1
         assert got["finish"][done].tolist() == [x for x, dn in zip(step["fin"], done) if dn], got["finish"]
+
+
+@pytest.mark.parametrize("advance", [False, True], ids=["plain", "planning"])
+@pytest.mark.parametrize("name", ["random", "statuses", "layered", "one-stage", "many-stages"])
+def test_state_image_equals_the_host_layout(name, advance):
+    """The state image that fate_pack_state builds in device memory (copies
+    and the list kernel) is the host packer's byte for byte, and so is the
+    image packed for a DAG handle in host memory (no kernel may read that)."""
+    w = {"random": lambda: synth.make_random_small(31, B=4, n=40, D=9, M=5, K=3, H=2, p_edge=0.6),
+         "statuses": lambda: synth.make_workload("layered-1024x200-d8", B=7, mark_statuses=True),
+         "layered": lambda: synth.make_workload("shards-1024x500-d16", B=5),
+         "one-stage": lambda: synth.make_random_small(33, B=1, n=1, D=2, M=2, K=1, H=1),
+         "many-stages": lambda: synth.make_random_small(34, B=2, n=1100, D=4, M=3, K=2, H=1, p_edge=0.004)}[name]()
+    print("[commit] state image", name, advance, flush=True)
+    pk = fate.fate_pack_dags(w)
+    hbuf, hd, hi = fate.fate_layout_dags(w)
+    st = fate.fate_pack_state(pk, w, advance=advance)
+    host = fate.PackedDags(pk.buf, hd, hi)
+    st2 = fate.fate_pack_state(host, w, advance=advance)
+    got, want = st.buf.cpu().numpy(), st2.buf.cpu().numpy()
+    assert got.shape == want.shape and np.array_equal(got, want)
+    if not advance:
+        img, h, _ = fate.fate_layout_state(hd, w)
+        assert np.array_equal(got[:len(img)], img)
+    assert (st.n_frontier, st.n_cand, st.handle.n_slices) == (st2.n_frontier, st2.n_cand, st2.handle.n_slices)
