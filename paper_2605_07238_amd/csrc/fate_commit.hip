@@ -1,7 +1,7 @@
 // Commit-and-advance of a planning state on the device (Alg. 1: materialise
 // the selected placements, then advance the planning frontier and update the
 // planning state; Alg. 2: commit into the action pool and update the state
-// as the stages complete).  Three launches on the caller's stream; only the
+// as the stages complete).  Two or three launches on the caller's stream; only the
 // instances' own frontiers and the children of the stages completed are
 // visited, never the whole batch:
 //
@@ -92,21 +92,24 @@ constexpr int kParBatch = 8;
 // stage's prefix group and model, and the candidate's size k.
 struct SlotL {
     uint64_t win, hash, wm;  // wm: the model's weight
-    double k;
-    int32_t model, i0;       // i0: the window's first device
-    double ready[FATE_MAX_SHARD];  // when the inputs are on window device i0 + p
+    uint16_t model, k;
+    int32_t i0;              // the window's first device
+    double ready[FATE_MAX_SHARD];  // when the inputs are on window device i0 + p; then its shard's finish
 };
+static_assert(sizeof(SlotL) == 64, "SlotL");
 
 // Prefix-slot rows in LDS are padded to a multiple of 8 entries so that a
 // row is searched 8 entries per batch of loads.
 __host__ __device__ inline int padded_slots(int K) { return (K + 7) & ~7; }
 
-// LDS of k_commit_apply: the staged slots and their shards' finish times,
-// the exec and switch tables, the model weights and fit masks, the instance's
-// prefix-slot rows and each row's ring head, then the instance's bitmap when
-// it is kept in LDS (bm_words words).
+// LDS of k_commit_apply: the staged slots, the exec and switch tables, the
+// model weights and fit masks, the instance's prefix-slot rows and each row's
+// ring head, then the instance's bitmap when it is kept in LDS (bm_words
+// words): 8.2 KB for 16 devices, 16 slots and 12 models, so that sixteen
+// one-wave workgroups fit a compute unit and all 4,096 fork-join instances run
+// at once (with the finish times apart, 10.6 KB, 256 of them started last).
 __host__ __device__ inline size_t apply_lds_bytes(int D, int M, int K, int bm_words) {
-    return 64 * sizeof(SlotL) + 64 * 8 * FATE_MAX_SHARD + 8 * (size_t)M * D + 16 * (size_t)M +
+    return 64 * sizeof(SlotL) + 8 * (size_t)M * D + 16 * (size_t)M +
            8 * (size_t)D * padded_slots(K) + 4 * (size_t)D + 4 * (size_t)bm_words;
 }
 
@@ -179,8 +182,7 @@ __global__ __launch_bounds__(64) void k_commit_apply(CommitLaunch a) {
     // largest frontiers first, so that the last waves to start are short
     const int b = (int)a.order[blockIdx.x], lane = threadIdx.x, D = a.D, K = a.K, M = a.M, Kp = padded_slots(K);
     SlotL *sl = reinterpret_cast<SlotL *>(smem);
-    double *sfin = reinterpret_cast<double *>(smem + (64 * sizeof(SlotL)) / 8);  // [64][FATE_MAX_SHARD]
-    uint64_t *wt = reinterpret_cast<uint64_t *>(sfin + 64 * FATE_MAX_SHARD);
+    uint64_t *wt = smem + (64 * sizeof(SlotL)) / 8;
     uint64_t *fit = wt + M;
     uint64_t *pslots = fit + M;
     float *ex = reinterpret_cast<float *>(pslots + (size_t)D * Kp);
@@ -241,9 +243,14 @@ __global__ __launch_bounds__(64) void k_commit_apply(CommitLaunch a) {
         bool rej = false;
         uint32_t s = 0, cb = 0, cn = 0;
         int kq = 0;
+        int j = -1;
         if (f < hi) {
             s = a.frontier[2 * f];
-            const int j = a.sel[f * a.sel_stride];
+            j = a.sel[f * a.sel_stride];
+        }
+        // only a selected slot needs its stage's record (one in seven on a
+        // fork-join frontier of 114 slots and 16 devices)
+        if (j >= 0) {
             const StageRec r = a.rec[s];
             cb = a.ch_off[s];
             cn = a.ch_off[s + 1] - cb;
@@ -252,33 +259,31 @@ __global__ __launch_bounds__(64) void k_commit_apply(CommitLaunch a) {
             x.model = r.model;
             x.wm = wt[r.model];
             x.i0 = 0;
-            x.k = 1.0;
-            if (j >= 0) {
-                if (j >= candidates_of(shard_cap_of(r.shard, a.max_shard, D), D)) {
+            x.k = 1;
+            if (j >= candidates_of(shard_cap_of(r.shard, a.max_shard, D), D)) {
+                rej = true;
+            } else {
+                int i0, k;
+                candidate_window(j, D, i0, k);
+                const uint64_t w = ((1ull << k) - 1ull) << i0;
+                if (((r.elig & fit[r.model]) & w) != w) {  // a device not eligible or too small
                     rej = true;
                 } else {
-                    int i0, k;
-                    candidate_window(j, D, i0, k);
-                    const uint64_t w = ((1ull << k) - 1ull) << i0;
-                    if (((r.elig & fit[r.model]) & w) != w) {  // a device not eligible or too small
-                        rej = true;
-                    } else {
-                        win = w;
-                        kq = k;
-                        x.k = (double)k;
-                        x.i0 = i0;
-                        // parents completed in earlier steps: their finish
-                        // times and holders are settled
-                        inputs_ready(a, r, i0, k, x.ready);
-                        a.holders[s] = w;
-                        a.status[s] = kCompleted;
-                    }
+                    win = w;
+                    kq = k;
+                    x.k = (uint16_t)k;
+                    x.i0 = i0;
+                    // parents completed in earlier steps: their finish
+                    // times and holders are settled
+                    inputs_ready(a, r, i0, k, x.ready);
+                    a.holders[s] = w;
+                    a.status[s] = kCompleted;
                 }
             }
             x.win = win;
             sl[lane] = x;
-            if (win == 0) mark(s);  // still pending: it stays in the frontier
         }
+        if (f < hi && win == 0) mark(s);  // still pending: it stays in the frontier
         rejected += (uint32_t)__popcll(__ballot(rej));
         // lane d collects the slots whose candidate contains device d
         uint64_t mine = 0;
@@ -291,7 +296,7 @@ __global__ __launch_bounds__(64) void k_commit_apply(CommitLaunch a) {
         while (live && mine) {
             const int q = __builtin_ctzll(mine);
             mine &= mine - 1;
-            const SlotL x = sl[q];
+            const SlotL &x = sl[q];
             const int m = x.model;
             const double ready = x.ready[d - x.i0];
             double start = tau > tn ? tau : tn;
@@ -323,14 +328,14 @@ __global__ __launch_bounds__(64) void k_commit_apply(CommitLaunch a) {
                     }
                 }
             }
-            tau = start + (x.k == 1.0 ? c : c / x.k) + sw;  // c / 1 is c
-            sfin[q * FATE_MAX_SHARD + (d - x.i0)] = tau;
+            tau = start + (x.k == 1 ? c : c / (double)x.k) + sw;  // c / 1 is c
+            sl[q].ready[d - x.i0] = tau;  // read by this lane only, until the barrier
         }
         __syncthreads();  // the next chunk overwrites the staged slots
         if (kq > 0) {  // the stage finishes with its latest shard
-            double fs = sfin[lane * FATE_MAX_SHARD];
+            double fs = sl[lane].ready[0];
             for (int p = 1; p < kq; ++p) {
-                const double t2 = sfin[lane * FATE_MAX_SHARD + p];
+                const double t2 = sl[lane].ready[p];
                 fs = t2 > fs ? t2 : fs;
             }
             a.fin[s] = (float)fs;
@@ -608,24 +613,94 @@ __global__ __launch_bounds__(1024) void k_commit_scan(CommitLaunch a) {
     }
 }
 
-__global__ __launch_bounds__(64) void k_commit_fill(CommitLaunch a) {
-    const int b = (int)a.order[blockIdx.x], lane = threadIdx.x;
-    const uint32_t F = a.fr_off[b], n = a.fr_off[b + 1] - F;
-    const uint2 cs = reinterpret_cast<const uint2 *>(a.base)[b];
+// Instance b's frontier slots from F on (n of them), with their instance,
+// candidate offsets from c0 and scoring slices from slice sl.
+__device__ __forceinline__ void fill_instance(const CommitLaunch &a, int b, uint32_t F, uint32_t n, uint32_t c0, uint32_t sl) {
+    const int lane = threadIdx.x;
     const uint2 *lst = reinterpret_cast<const uint2 *>(a.list) + a.stage_off[b];
     uint2 *fr = reinterpret_cast<uint2 *>(a.frontier);
     for (uint32_t i = lane; i < n; i += 64) {
         const uint2 e = lst[i];
         fr[F + i] = make_uint2(e.x, (uint32_t)b);
-        a.cand_off[F + i] = cs.x + e.y;
+        a.cand_off[F + i] = c0 + e.y;
     }
     const uint32_t slice = (uint32_t)a.slice, ns = (n + slice - 1u) / slice;
     for (uint32_t q = lane; q < ns; q += 64) {
-        const int64_t o = 3 * (int64_t)(cs.y + q);
+        const int64_t o = 3 * (int64_t)(sl + q);
         a.slices[o] = (uint32_t)b;
         a.slices[o + 1] = F + q * slice;
         a.slices[o + 2] = F + min(n, (q + 1u) * slice);
     }
+}
+
+__global__ __launch_bounds__(64) void k_commit_fill(CommitLaunch a) {
+    const int b = (int)a.order[blockIdx.x];
+    const uint32_t F = a.fr_off[b], n = a.fr_off[b + 1] - F;
+    const uint2 cs = reinterpret_cast<const uint2 *>(a.base)[b];
+    fill_instance(a, b, F, n, cs.x, cs.y);
+}
+
+// k_commit_scan and k_commit_fill in one launch for batches of at most
+// kFinishInstances: each instance's wave sums the totals of the instances
+// before it and finds its place in the dispatch order by itself (16 bytes per
+// instance, from the L2 after the first wave), so nothing waits for one
+// workgroup's scan; the first wave writes the counters.  At 32 layered
+// instances the two launches took 7.8 + 3.2 us; past kFinishInstances every
+// wave would read more than the scan as a whole does.
+constexpr int kFinishInstances = 1024;
+
+template <bool SLICES>
+__global__ __launch_bounds__(64) void k_commit_finish(CommitLaunch a) {
+    const int b = blockIdx.x, lane = threadIdx.x, B = a.B;
+    const uint4 *tot = reinterpret_cast<const uint4 *>(a.tot);
+    __shared__ uint32_t nfs[kFinishInstances];
+    auto sum64 = [](uint32_t x) {
+        uint32_t t = 0;
+        (void)wave_exscan_u32(x, t);
+        return t;
+    };
+    const uint4 own = tot[b];
+    uint32_t all[4] = {0u, 0u, 0u, 0u}, pre[3] = {0u, 0u, 0u}, mx = 0;
+    for (int i = lane; i < B; i += 64) {
+        const uint4 t = tot[i];
+        nfs[i] = t.x;
+        mx = max(mx, t.x);
+        all[0] += t.x; all[1] += t.y; all[2] += t.z; all[3] += t.w;
+        if (i < b) { pre[0] += t.x; pre[1] += t.y; pre[2] += t.z; }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    const uint32_t F = sum64(pre[0]), c0 = sum64(pre[1]);
+    uint32_t sl = sum64(pre[2]);  // slices in instance order
+    __syncthreads();
+    // the instance's place in the dispatch order: the larger classes, and the
+    // instances before it in its own
+    const uint32_t cls = order_class(own.x, mx);
+    uint32_t before = 0, sbefore = 0;
+    for (int i = lane; i < B; i += 64) {
+        const uint32_t n = nfs[i], q = order_class(n, mx);
+        if (q < cls || (q == cls && i < b)) {
+            ++before;
+            sbefore += (n + (uint32_t)a.slice - 1u) / (uint32_t)a.slice;
+        }
+    }
+    const uint32_t pos = sum64(before);
+    if (SLICES) sl = sum64(sbefore);
+    if (lane == 0) {
+        a.order[pos] = (uint32_t)b;
+        a.fr_off[b] = F;
+    }
+    if (b == 0) {  // uniform
+#pragma unroll
+        for (int q = 0; q < 4; ++q) all[q] = sum64(all[q]);
+        if (lane == 0) {
+            a.fr_off[B] = all[0];
+            a.cand_off[all[0]] = all[1];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a.counts[q] = all[q];
+        }
+    }
+    fill_instance(a, b, F, own.x, c0, sl);
 }
 
 // The completed-parent lists of a state being packed, one thread per stage
@@ -683,6 +758,11 @@ int launch_commit(const CommitLaunch &a, void *stream) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const size_t lds = apply_lds_bytes(a.D, a.M, a.K, a.bm_lds ? a.bm_words : 0);
     if (a.B > 0) hipLaunchKernelGGL(k_commit_apply, dim3((unsigned)a.B), dim3(64), lds, s, a);
+    if (a.B > 0 && a.B <= kFinishInstances) {
+        if (a.slice_order) hipLaunchKernelGGL(k_commit_finish<true>, dim3((unsigned)a.B), dim3(64), 0, s, a);
+        else hipLaunchKernelGGL(k_commit_finish<false>, dim3((unsigned)a.B), dim3(64), 0, s, a);
+        return (int)hipGetLastError();
+    }
     if (a.slice_order) hipLaunchKernelGGL(k_commit_scan<true>, dim3(1), dim3(1024), 0, s, a);
     else hipLaunchKernelGGL(k_commit_scan<false>, dim3(1), dim3(1024), 0, s, a);
     if (a.B > 0) hipLaunchKernelGGL(k_commit_fill, dim3((unsigned)a.B), dim3(64), 0, s, a);

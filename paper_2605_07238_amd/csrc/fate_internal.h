@@ -171,8 +171,8 @@ inline bool rows_batch(const fate_dags_t *dags, int max_shard, int K) {
 // within 2% of a full sort by size in a model of the fork-join launch.
 constexpr int kOrderClasses = 8;
 __host__ __device__ inline uint32_t order_class(uint32_t n, uint32_t mx) {
-    const uint64_t c = (uint64_t)n * kOrderClasses / ((uint64_t)mx + 1u);
-    return (uint32_t)(kOrderClasses - 1) - (uint32_t)(c < kOrderClasses - 1 ? c : kOrderClasses - 1);
+    const uint32_t c = n * (uint32_t)kOrderClasses / (mx + 1u);  // below 2^28 stages: no overflow
+    return (uint32_t)(kOrderClasses - 1) - (c < (uint32_t)kOrderClasses - 1u ? c : (uint32_t)kOrderClasses - 1u);
 }
 
 // Bitmap words past which an instance's frontier bitmap moves from LDS to

@@ -431,3 +431,31 @@ def test_state_image_equals_the_host_layout(name, advance):
         img, h, _ = fate.fate_layout_state(hd, w)
         assert np.array_equal(got[:len(img)], img)
     assert (st.n_frontier, st.n_cand, st.handle.n_slices) == (st2.n_frontier, st2.n_cand, st2.handle.n_slices)
+
+
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 1024, 1025])
+@pytest.mark.parametrize("windows", [False, True], ids=["rows", "slices"])
+def test_commit_around_the_one_launch_finish(B, windows):
+    """Batches on both sides of the largest that the fill finishes without the
+    scan, whose slices do or do not follow the dispatch order."""
+    w = synth.make_random_small(50 + B, B=B, n=9, D=4, M=3, max_shard=2 if windows else 1,
+                                shard_frac=0.3 if windows else 0.0, p_edge=0.3, uniform_beta=not windows)
+    _run_steps(w, 2)
+
+
+def test_commit_many_children_per_chunk():
+    """More than 64 (stage, child) pairs in a pass, children with more than
+    eight parents, frontiers of one, two and three chunks."""
+    insts = []
+    rng = np.random.default_rng(3)
+    for roots in (40, 70, 150):
+        parents = [[] for _ in range(roots)]
+        for c in range(3 * roots):
+            parents.append(sorted(rng.choice(roots, size=1 + c % 12, replace=False).tolist()))
+        n = len(parents)
+        insts.append(dict(parents=parents, model=[v % 3 for v in range(n)], elig=[(1 << 6) - 1] * n,
+                          prefix_hash=[v % 5 for v in range(n)], prefix_tokens=[100.0] * n, out_bytes=[1e8 * (1 + v % 3) for v in range(n)],
+                          status=[0] * n, holders=[0] * n, resident=[0] * 6, tau_free=[0.1 * d for d in range(6)], t_now=0.0))
+    spec = dict(D=6, M=3, K=2, exec=[[1.0, 1.5, 2.0, 0.5, 0.75, 1.25]] * 3, switch_s=[[0.25] * 6] * 3, weight_gb=[10, 12, 14],
+                cap_gb=[25] * 6, beta=[[0.0 if i == j else 2e-10 for j in range(6)] for i in range(6)], max_shard=1, instances=insts)
+    _run_steps(builders.from_spec(spec, H=1), 4)
