@@ -182,3 +182,24 @@ def test_plan_errors():
     sel = fate.fate_plan_wave(st, idx[:, :4].contiguous(), val[:, :4].contiguous())
     torch.cuda.synchronize()
     assert np.all(sel.cpu().numpy() == -1)  # nothing valid to take
+
+
+@pytest.mark.parametrize("D", [5, 32, 33, 64])
+@pytest.mark.parametrize("roots,k", [(1, 1), (64, 1), (128, 4), (129, 4), (256, 4), (257, 4), (16, 64), (20, 25)])
+def test_plan_choice_counts(D, roots, k):
+    """Instances around 64 lanes of eight and of sixteen register choices and
+    past them, with ties across lanes and rows, windows, 32- and 64-bit masks."""
+    w = synth.make_random_small(90 + D, B=2, n=roots + 12, D=D, M=3, K=1, max_shard=4, shard_frac=0.4, p_edge=0.0)
+    w.status[:] = 0
+    w.holders[:] = 0
+    drop = np.zeros(w.N, bool)
+    for b in range(w.B):  # exactly `roots` pending stages per instance
+        lo = int(w.stage_off[b])
+        drop[lo + roots:int(w.stage_off[b + 1])] = True
+    w.status[drop] = 1
+    w.holders[drop] = 1
+    f_off, n_cand, idx, val = synthetic_choices(w, k, 7 * roots + k)
+    assert np.all(np.diff(f_off) == roots)
+    print("[plan] choices", D, roots, k, flush=True)
+    want, _ = oracle.plan_wave(w.D, f_off, n_cand, idx, val)
+    assert np.array_equal(_gpu_plan(w, idx, val), want)
