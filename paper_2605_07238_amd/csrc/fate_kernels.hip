@@ -590,13 +590,15 @@ __device__ __forceinline__ uint32_t topk_bits(float x) { return x > -inf_f() ? o
 constexpr int kLaneTopk = 4;
 constexpr uint32_t kRankedInLoop = 0xffffffffu;
 
-// Top-k (k <= kLaneTopk) of up to 16 candidates held by one lane as score
-// bits x[0..15] (0 for none or -inf): each candidate, in index order, enters
+// Top-k (k <= kLaneTopk) of up to N candidates held by one lane as score
+// bits x[0..N-1] (0 for none or -inf): each candidate, in index order, enters
 // a list sorted by bits descending and displaces only strictly smaller
 // entries, so among equal scores the lower index ranks first.  The pick is
 // (index, score), or (-1, -inf) once the candidates run out.
 template <int N>
-__device__ __forceinline__ void lane_rank(const uint32_t (&x)[N], uint32_t (&t)[kLaneTopk], int32_t (&ix)[kLaneTopk]) {
+__device__ __forceinline__ void lane_topk(const uint32_t (&x)[N], int k, int32_t *out_i, float *out_v) {
+    uint32_t t[kLaneTopk];
+    int32_t ix[kLaneTopk];
 #pragma unroll
     for (int r = 0; r < kLaneTopk; ++r) { t[r] = 0u; ix[r] = -1; }
 #pragma unroll
@@ -613,11 +615,6 @@ __device__ __forceinline__ void lane_rank(const uint32_t (&x)[N], uint32_t (&t)[
         t[0] = gt[0] ? c : t[0];
         ix[0] = gt[0] ? j : ix[0];
     }
-}
-__device__ __forceinline__ void lane_topk16(const uint32_t (&x)[16], int k, int32_t *out_i, float *out_v) {
-    uint32_t t[kLaneTopk];
-    int32_t ix[kLaneTopk];
-    lane_rank(x, t, ix);
 #pragma unroll
     for (int r = 0; r < kLaneTopk; ++r) {
         if (r < k) {
@@ -1685,7 +1682,7 @@ void k_score(ScoreLaunch a) {
             }
             if (x[0] == kRankedInLoop) continue;
             const int64_t f = (int64_t)f0 + i;
-            lane_topk16(x, a.topk, a.tk_idx + f * a.topk, a.tk_val + f * a.topk);
+            lane_topk(x, a.topk, a.tk_idx + f * a.topk, a.tk_val + f * a.topk);
         }
     }
 }
@@ -1746,14 +1743,12 @@ __global__ __launch_bounds__(kBlock) void k_topk_lane(TopkLaunch a) {
 #pragma unroll
             for (int q = 0; q < ND; ++q) x[q] = q < D ? scores[f * D + q] : -inf_f();
         }
-        uint32_t bits[ND], t[kLaneTopk];
+        uint32_t bits[ND];
         int32_t ix[kLaneTopk];
-#pragma unroll
-        for (int q = 0; q < ND; ++q) bits[q] = topk_bits(x[q]);
-        lane_rank(bits, t, ix);
         float v[kLaneTopk];
 #pragma unroll
-        for (int r = 0; r < kLaneTopk; ++r) v[r] = t[r] != 0u ? order_bits_inv(t[r]) : -inf_f();
+        for (int q = 0; q < ND; ++q) bits[q] = topk_bits(x[q]);
+        lane_topk(bits, kLaneTopk, ix, v);
         int32_t *oi = a.idx + oo + f * k;
         float *ov = a.val + oo + f * k;
         if (a.vout) {  // uniform
@@ -2278,7 +2273,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
 #pragma unroll
                 for (int q = 0; q < 16; ++q) x[q] = q < ND ? slot[q] : 0u;
                 const int64_t f = fc + tid;
-                lane_topk16(x, a.topk, a.tk_idx + f * a.topk, a.tk_val + f * a.topk);
+                lane_topk(x, a.topk, a.tk_idx + f * a.topk, a.tk_val + f * a.topk);
             }
         }
         if (c0 + kRowsChunk < nFi) __syncthreads();  // uniform: the next chunk reuses the stage slots and task sums
@@ -2309,7 +2304,14 @@ struct alignas(16) StageR4 {
 static_assert(sizeof(StageR4) == 80, "StageR4");
 
 constexpr int kRows4Devs = 64;                       // devices a row can span
-constexpr int kRows4Stride = 2 * kRows4Devs + 4;     // floats per model row of the cost table
+// Floats per model row of each of the two cost tables, (exec + switch term) and
+// the signed switch magnitude: a row reads the first before its minimum and the
+// second after it, sixteen bytes per lane and load; the four floats more start
+// rows of different models on different banks.  As one table of pairs the reads
+// were strided eight-byte ones, and the power-law batch took 74.1 us (58.2).
+// (k_rows keeps the pairs: whole float4s there cost it five spilled registers,
+// 380 against 394 us on a 14-set sweep.)
+constexpr int kRows4Stride = kRows4Devs + 4;
 
 struct Rows4Plan {
     uint32_t pkey, pmask, rho, cap, wt, fits, wait, gpow, rtab, flf, stages, tasks, part, misc, total;
@@ -2332,7 +2334,7 @@ __host__ __device__ inline Rows4Plan rows4_plan(int D, int K, int M, int blk) {
     q.wait = o; o += 4 * kRows4Devs;
     q.gpow = o; o += 4 * 16;
     o = (o + 15u) & ~15u;
-    q.rtab = o; o += 4 * (uint32_t)(M * kRows4Stride);
+    q.rtab = o; o += 8 * (uint32_t)(M * kRows4Stride);
     o = (o + 7u) & ~7u;
     q.flf = o; o += 8 * (uint32_t)(M * M);
     o = (o + 15u) & ~15u;
@@ -2386,7 +2388,7 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
     uint64_t *fits = reinterpret_cast<uint64_t *>(sb + plan.fits);
     float *wait = reinterpret_cast<float *>(sb + plan.wait);
     float *gpow = reinterpret_cast<float *>(sb + plan.gpow);
-    float *rtab = reinterpret_cast<float *>(sb + plan.rtab);
+    float *rtab = reinterpret_cast<float *>(sb + plan.rtab), *rks = rtab + M * CS;
     uint64_t *flf = reinterpret_cast<uint64_t *>(sb + plan.flf);  // per (m(v), m(w)): devices where Load flips m(w)
     StageR4 *stg = reinterpret_cast<StageR4 *>(sb + plan.stages);
     uint32_t *tasks = reinterpret_cast<uint32_t *>(sb + plan.tasks);
@@ -2425,8 +2427,8 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             if (!bit(a.fits[m], d)) sw0 = inf_f();
             sks = res ? ks + ps.lam_m : -(ks + ps.lam_m);
         }
-        rtab[m * CS + 2 * d] = sw0;  // devices past D: never feasible
-        rtab[m * CS + 2 * d + 1] = sks;
+        rtab[m * CS + d] = sw0;  // devices past D: never feasible
+        rks[m * CS + d] = sks;
     }
     constexpr int kPre = 4;  // prefix-cache entries fetched before the barrier
     uint64_t pre[kPre];
@@ -2601,14 +2603,18 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
                 const float pfp = lam_p * ps.kpf * rw.tokens;
                 const float cw = lam_c * fast_rcp((float)rw.npar);  // a descendant has at least one parent
                 const uint32_t flip = (uint32_t)((flf[mrow + mw] >> dq) & 0xffffull);
-                const float *crow = rtab + mw * CS + 2 * dq;
+                const float *crow = rtab + mw * CS + dq, *krow = rks + mw * CS + dq;
                 // B without the completed parents: cost with the switch term, less the prefix benefit
                 float B[ND];
 #pragma unroll
-                for (int j = 0; j < ND / 2; ++j) {
+                for (int j = 0; j < ND / 4; ++j) {
                     const float4 c = *reinterpret_cast<const float4 *>(crow + 4 * j);
-                    B[2 * j] = c.x - __uint_as_float(__float_as_uint(pfp) & (uint32_t)__builtin_amdgcn_sbfe((int)pfo, 2 * j, 1u));
-                    B[2 * j + 1] = c.z - __uint_as_float(__float_as_uint(pfp) & (uint32_t)__builtin_amdgcn_sbfe((int)pfo, 2 * j + 1, 1u));
+                    const float cq[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int d = 4 * j + u;
+                        B[d] = cq[u] - __uint_as_float(__float_as_uint(pfp) & (uint32_t)__builtin_amdgcn_sbfe((int)pfo, d, 1u));
+                    }
                 }
                 // completed parents: every one's transfer (all remote), and on the
                 // devices holding one its transfer saved and the colocation share
@@ -2660,14 +2666,15 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
                 // devices that gain grp(w) once v runs there
                 const uint32_t gain = same ? (~pfo & qmask) : 0u;
 #pragma unroll
-                for (int j = 0; j < ND / 2; ++j) {
-                    const float4 c = *reinterpret_cast<const float4 *>(crow + 4 * j);
+                for (int j = 0; j < ND / 4; ++j) {
+                    const float4 c = *reinterpret_cast<const float4 *>(krow + 4 * j);
+                    const float kq[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int d = 2 * j + u;
+                    for (int u = 0; u < 4; ++u) {
+                        const int d = 4 * j + u;
                         // m(w)'s switch term on d changes by the signed magnitude
                         // where v's Load flips m(w)'s residency there
-                        const float dsw = __uint_as_float(__float_as_uint(u == 0 ? c.y : c.w) & (uint32_t)__builtin_amdgcn_sbfe((int)flip, d, 1u));
+                        const float dsw = __uint_as_float(__float_as_uint(kq[u]) & (uint32_t)__builtin_amdgcn_sbfe((int)flip, d, 1u));
                         const float gp = __uint_as_float(__float_as_uint(pfp) & (uint32_t)__builtin_amdgcn_sbfe((int)gain, d, 1u));
                         const float C = (B[d] + dsw) - gp;
                         const float o = B[d] == m1 ? m2c : m1c;
@@ -2726,7 +2733,7 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             // the switch term where m(v) is not resident (the row table's
             // magnitude is negative there, and holds the same-model weight too)
             const float swo = bit(rho[dl], s.model) ? 0.0f - ps.lam_m
-                              : ps.lam_m == 0.0f    ? -rtab[s.model * CS + 2 * dl + 1]
+                              : ps.lam_m == 0.0f    ? -rks[s.model * CS + dl]
                                                     : ps.lam_s * a.ksw[s.model * D + dl];
             const float ex = a.exec[s.model * D + dl];
             const float pf_v = ((s.pfm >> dl) & 1ull) ? ps.kpf * s.tokens : 0.0f;
