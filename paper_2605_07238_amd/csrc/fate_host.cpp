@@ -746,6 +746,17 @@ bool on_same_gpu(const fate_dags_t *pk, const void *d_buf) {
     return x.type == hipMemoryTypeDevice && y.type == hipMemoryTypeDevice && x.device == y.device;
 }
 
+// Whether the lists of a packed state are gathered on the host: where no kernel
+// may read the DAGs, and for small images, whose one copy costs less than the
+// dozen copies and the launch of the other way (about 100 us; a host gathers
+// and copies some 350 KB in that time).
+constexpr int64_t kSmallImage = 512 * 1024;
+bool lists_on_host(const fate_dags_t *pk, const fate_state_t *st, const void *d_buf) {
+    if (!pk || !st) return true;
+    const int64_t bytes = 16 * pk->E + 12 * pk->N + 8 * (int64_t)pk->B * pk->D * (std::max(0, st->K) + 2);
+    return bytes < kSmallImage || !on_same_gpu(pk, d_buf);
+}
+
 // A packed state's image: sections and kernel, or (lists) the host's image
 // copied whole.
 fate_status_t pack_state_image(const fate_dags_t *pk, const fate_dag_batch_t *g, const fate_state_t *st,
@@ -901,7 +912,7 @@ fate_status_t fate_pack_state(const fate_dags_t *packed, const fate_dag_batch_t 
                               const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                               void *stream, fate_state_h *out) {
     if (!d_buf || !out) return FATE_EINVAL;
-    const bool lists = !packed || !on_same_gpu(packed, d_buf);
+    const bool lists = lists_on_host(packed, state, d_buf);
     StatePlan p;
     fate_status_t st = plan_state(packed, dags, state, max_shard, lists, &p);
     if (st != FATE_OK) return st;
@@ -930,7 +941,7 @@ fate_status_t fate_pack_state_advance(const fate_dags_t *packed, const fate_dag_
                                       const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                                       void *stream, fate_state_h *out) {
     if (!d_buf || !out) return FATE_EINVAL;
-    const bool lists = !packed || !on_same_gpu(packed, d_buf);
+    const bool lists = lists_on_host(packed, state, d_buf);
     StatePlan p;
     fate_status_t st = plan_state(packed, dags, state, max_shard, lists, &p);
     if (st != FATE_OK) return st;

@@ -409,16 +409,16 @@ def test_commit_inputs_ready_scenario():
 
 
 @pytest.mark.parametrize("advance", [False, True], ids=["plain", "planning"])
-@pytest.mark.parametrize("name", ["random", "statuses", "layered", "one-stage", "many-stages"])
+@pytest.mark.parametrize("name", ["small", "one-stage", "statuses", "layered", "many-stages"])
 def test_state_image_equals_the_host_layout(name, advance):
     """The state image that fate_pack_state builds in device memory (copies
     and the list kernel) is the host packer's byte for byte, and so is the
     image packed for a DAG handle in host memory (no kernel may read that)."""
-    w = {"random": lambda: synth.make_random_small(31, B=4, n=40, D=9, M=5, K=3, H=2, p_edge=0.6),
-         "statuses": lambda: synth.make_workload("layered-1024x200-d8", B=7, mark_statuses=True),
-         "layered": lambda: synth.make_workload("shards-1024x500-d16", B=5),
+    w = {"small": lambda: synth.make_random_small(31, B=4, n=40, D=9, M=5, K=3, H=2, p_edge=0.6),
          "one-stage": lambda: synth.make_random_small(33, B=1, n=1, D=2, M=2, K=1, H=1),
-         "many-stages": lambda: synth.make_random_small(34, B=2, n=1100, D=4, M=3, K=2, H=1, p_edge=0.004)}[name]()
+         "statuses": lambda: synth.make_workload("layered-1024x200-d8", B=130, mark_statuses=True),
+         "layered": lambda: synth.make_workload("shards-1024x500-d16", B=50),
+         "many-stages": lambda: synth.make_workload("powerlaw-256x10000-d64", B=3)}[name]()
     print("[commit] state image", name, advance, flush=True)
     pk = fate.fate_pack_dags(w)
     hbuf, hd, hi = fate.fate_layout_dags(w)
