@@ -472,7 +472,7 @@ __global__ __launch_bounds__(64) void k_sim(SimLaunch a) {
 //           stage i; a placement that changes a device's slots updates all
 //           64 masks with two comparisons.
 struct SimPlan {
-    uint32_t rank, key, idx, ring, par, tab, fits, beta, total;
+    uint32_t rank, key, idx, ring, par, tab, fits, wts, beta, total;
 };
 constexpr int kParBuf = 256;  // prefetched parents of 64 stages
 
@@ -500,6 +500,7 @@ __host__ __device__ inline SimPlan sim_plan(int64_t max_stages, int D, int K, in
     q.par = o; o += (uint32_t)sizeof(ParL) * (uint32_t)kParBuf;
     q.tab = o; o += 8 * (uint32_t)(M * D);
     q.fits = o; o += 8 * (uint32_t)M;
+    q.wts = o; o += 8 * (uint32_t)M;
     q.beta = o; o += uni ? 0u : 4 * (uint32_t)(D * D);
     q.total = (o + 15u) & ~15u;
     return q;
@@ -594,7 +595,7 @@ __global__ __launch_bounds__(64) void k_sim_lds(SimLaunch a) {
     uint64_t *ring = reinterpret_cast<uint64_t *>(sb + pl.ring);
     ParL *pbuf = reinterpret_cast<ParL *>(sb + pl.par);
     float2 *tab = reinterpret_cast<float2 *>(sb + pl.tab);  // (run time, switch time) of model m on device d
-    uint64_t *fits = reinterpret_cast<uint64_t *>(sb + pl.fits);
+    uint64_t *fits = reinterpret_cast<uint64_t *>(sb + pl.fits), *wts = reinterpret_cast<uint64_t *>(sb + pl.wts);
     float *bt = reinterpret_cast<float *>(sb + pl.beta);
 
     const int64_t base = a.stage_off[b];
@@ -604,22 +605,30 @@ __global__ __launch_bounds__(64) void k_sim_lds(SimLaunch a) {
     const int dl = live ? lane : D - 1;
     const uint64_t dm = D >= 64 ? ~0ull : ((1ull << D) - 1ull);
     for (int i = lane; i < M * D; i += 64) tab[i] = make_float2(a.exec[i], a.ksw[i]);
-    if (lane < M) fits[lane] = a.fits[lane];
+    if (lane < M) {
+        fits[lane] = a.fits[lane];
+        wts[lane] = a.weight[lane];
+    }
     if (!UNI)
         for (int i = lane; i < D * D; i += 64) bt[i] = a.beta[i];
     for (int i = lane; i < D * K; i += 64) ring[i] = a.pcache[(int64_t)b * D * K + i];
     double fr = live ? fmax((double)a.tau[(int64_t)b * D + lane], t0) : 0.0;  // lane d: free time of device d
     uint64_t res = live ? a.resident[(int64_t)b * D + lane] : 0ull;           // its resident models
     const uint64_t cap = live ? a.cap[lane] : 0ull;
-    const uint64_t wt = lane < M ? a.weight[lane] : 0ull;  // lane m: weight of model m
-    uint64_t tot = 0;                                      // lane d: weight of the resident models
-    for (int m = 0; m < M; ++m) tot += ((res >> m) & 1ull) ? rl64(wt, m) : 0ull;
     int lastm = -1;  // lane d: model of the stage device d ran last
     const double b0 = (double)a.beta0;
     lds_order();
-    uint32_t emask = 0, head = 0;  // lane d: empty slots of device d; its oldest slot once none is empty
-    if (live)
+    uint64_t tot = 0;  // lane d: weight of the resident models
+    for (int m = 0; m < M; ++m) tot += ((res >> m) & 1ull) ? wts[m] : 0ull;
+    // lane d: the empty slots of device d, the slot the next group takes (the
+    // first empty one, or the oldest) and what it holds
+    uint32_t emask = 0, pos = 0;
+    uint64_t victim = 0;
+    if (live && K > 0) {
         for (int e = 0; e < K; ++e) emask |= (ring[lane * K + e] == 0 ? 1u : 0u) << e;
+        pos = emask ? (uint32_t)__builtin_ctz(emask) : 0u;
+        victim = ring[lane * K + (int)pos];
+    }
 
     // ---- the stages to run and their order
     int cnt = 0;
@@ -825,38 +834,38 @@ __global__ __launch_bounds__(64) void k_sim_lds(SimLaunch a) {
             for (uint64_t t = h; t; t &= t - 1) x = fmin(x, (double)bt[__builtin_ctzll(t) * D + d]);
             return x;
         };
-        // stage i's group joins the slots of device d (uniform), which lacks
-        // it: the first empty slot, else the oldest
+        // stage i's group joins the slots of device d (uniform), which lacks it
         auto join_slots = [&](int i, int d) {
-            const uint64_t hash = rl64(bhash, i);
+            const uint64_t hash = rl64(bhash, i), old = rl64(victim, d);
             if (hash == 0 || K == 0) return;
-            const uint32_t em = (uint32_t)__builtin_amdgcn_readlane((int)emask, d);
-            int e;
-            if (em) {
-                e = __builtin_ctz(em);
-                emask = lane == d ? em & (em - 1u) : emask;
-            } else {
-                e = __builtin_amdgcn_readlane((int)head, d);
-                head = lane == d ? (uint32_t)(e + 1 == K ? 0 : e + 1) : head;
+            // the group dropped leaves the device unless another slot has it too
+            // (an initial state may repeat one); seldom does a stage of the
+            // batch ask for it
+            if (old != 0 && __ballot(bhash == old) != 0) {
                 const uint64_t row = lane < K ? ring[d * K + lane] : 0ull;
-                const uint64_t old = rl64(row, e);
-                // the group dropped leaves the device unless another slot has it too
-                if ((__ballot(row == old) & ~(1ull << e)) == 0) cached &= bhash == old ? ~(1ull << d) : ~0ull;
+                if (__popcll(__ballot(row == old)) == 1) cached &= bhash == old ? ~(1ull << d) : ~0ull;
             }
             cached |= bhash == hash ? 1ull << d : 0ull;
-            if (lane == 0) ring[d * K + e] = hash;
+            if (lane == d) {
+                ring[d * K + (int)pos] = hash;
+                const uint32_t left = emask & (emask - 1u);  // pos was the lowest of them
+                const uint32_t next = pos + 1u == (uint32_t)K ? 0u : pos + 1u;
+                pos = emask == 0 ? next : left ? (uint32_t)__builtin_ctz(left) : 0u;
+                emask = emask ? left : 0u;
+                victim = ring[d * K + (int)pos];
+            }
         };
         // device d (uniform) loads model m, which it lacks
         auto load = [&](int d, int m) {
-            uint64_t rs = rl64(res, d) | 1ull << m, tt = rl64(tot, d) + rl64(wt, m);
-            const uint64_t cp = rl64(cap, d);
-            for (uint64_t t = rs & ~(1ull << m); t && tt > cp; t &= t - 1) {
-                const int x = __builtin_ctzll(t);
-                rs &= ~(1ull << x);
-                tt -= rl64(wt, x);
+            if (lane == d) {
+                res |= 1ull << m;
+                tot += wts[m];
+                for (uint64_t t = res & ~(1ull << m); t && tot > cap; t &= t - 1) {
+                    const int x = __builtin_ctzll(t);
+                    res &= ~(1ull << x);
+                    tot -= wts[x];
+                }
             }
-            res = lane == d ? rs : res;
-            tot = lane == d ? tt : tot;
         };
 
         for (int i = 0; i < nb; ++i) {  // uniform
