@@ -2035,34 +2035,36 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             const uint32_t f0n = n0 / Lr, f1n = n1 / Lr, t0n = n0 - f0n * Lr, t1n = n1 - f1n * Lr;
             uint32_t nfull = 0;
             const uint32_t off = wave_exscan_u32(f0n + f1n, nfull);
-            // tail tasks by length buckets, longest first: a count per bucket,
-            // then each tail takes the next slot of its bucket (which lane
-            // runs which task does not change any sum: a stage adds its full
-            // tasks, then its tail)
-            uint32_t *bkt = reinterpret_cast<uint32_t *>(partf);  // scratch until the rows write their sums
-            constexpr uint32_t kBuckets = 32;
-            auto bucket = [&](uint32_t len) { return len >= kBuckets ? kBuckets - 1u : len; };
-            if (tid < (int)kBuckets) bkt[tid] = 0u;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (i0 < nC && t0n) atomicAdd(&bkt[bucket(t0n)], 1u);
-            if (i1 < nC && t1n) atomicAdd(&bkt[bucket(t1n)], 1u);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint32_t cb = tid < (int)kBuckets ? bkt[kBuckets - 1u - (uint32_t)tid] : 0u;  // longest first
-            uint32_t ntail = 0;
-            const uint32_t start = nfull + wave_exscan_u32(cb, ntail);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (tid < (int)kBuckets) bkt[kBuckets - 1u - (uint32_t)tid] = start;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint32_t k0 = (i0 < nC && t0n) ? atomicAdd(&bkt[bucket(t0n)], 1u) : 0u;
-            const uint32_t k1 = (i1 < nC && t1n) ? atomicAdd(&bkt[bucket(t1n)], 1u) : 0u;
+            uint32_t ntail = 0, k0 = 0, k1 = 0;
+            if (Lr > 1) {  // uniform; one-row tasks leave no tails
+                // tail tasks by length buckets, longest first: a count per bucket,
+                // then each tail takes the next slot of its bucket (which lane
+                // runs which task does not change any sum: a stage adds its full
+                // tasks, then its tail)
+                uint32_t *bkt = reinterpret_cast<uint32_t *>(partf);  // scratch until the rows write their sums
+                constexpr uint32_t kBuckets = 32;
+                auto bucket = [&](uint32_t len) { return len >= kBuckets ? kBuckets - 1u : len; };
+                if (tid < (int)kBuckets) bkt[tid] = 0u;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                if (i0 < nC && t0n) atomicAdd(&bkt[bucket(t0n)], 1u);
+                if (i1 < nC && t1n) atomicAdd(&bkt[bucket(t1n)], 1u);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const uint32_t cb = tid < (int)kBuckets ? bkt[kBuckets - 1u - (uint32_t)tid] : 0u;  // longest first
+                const uint32_t start = nfull + wave_exscan_u32(cb, ntail);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                if (tid < (int)kBuckets) bkt[kBuckets - 1u - (uint32_t)tid] = start;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                k0 = (i0 < nC && t0n) ? atomicAdd(&bkt[bucket(t0n)], 1u) : 0u;
+                k1 = (i1 < nC && t1n) ? atomicAdd(&bkt[bucket(t1n)], 1u) : 0u;
+            }
             if (i0 < nC) {
                 stg[i0].q0 = off | (f0n << 16);
                 stg[i0].nq = t0n ? k0 : 0xffffffffu;
