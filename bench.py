@@ -403,7 +403,7 @@ def planning_loop(w, pk, params, k, steps, log, full_plan=True, max_waves=2000):
         out.update(commit_ms_mean=float(np.mean(cms)), plan_ms_mean=float(np.mean([r["plan_ms"] for r in timed])),
                    step_ms_mean=float(np.mean([r["score_topk_ms"] + r["plan_ms"] + r["commit_ms"] for r in timed])),
                    commit_roofline={"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                                    "frac": achieved / HBM_PEAK_GBS, "kernels": "fate_commit_advance (3 launches)"})
+                                    "frac": achieved / HBM_PEAK_GBS, "kernels": "fate_commit_advance (2 launches, 3 above 1,024 instances)"})
     if full_plan:
         # the rest of the plan, untimed per launch: one event pair around the whole loop
         n = len(rows)

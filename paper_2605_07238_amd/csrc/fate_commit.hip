@@ -1,7 +1,8 @@
 // Commit-and-advance of a planning state on the device (Alg. 1: materialise
 // the selected placements, then advance the planning frontier and update the
 // planning state; Alg. 2: commit into the action pool and update the state
-// as the stages complete).  Two or three launches on the caller's stream; only the
+// as the stages complete).  Two launches on the caller's stream for up to 1,024
+// instances (apply, finish), three for more (apply, scan, fill); only the
 // instances' own frontiers and the children of the stages completed are
 // visited, never the whole batch:
 //

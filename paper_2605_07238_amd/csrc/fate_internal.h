@@ -247,7 +247,7 @@ struct ListsLaunch {
 int launch_lists(const ListsLaunch &a, void *stream);
 
 // Commit-and-advance behind both entry points (fate_host.cpp): validation,
-// then the three launches with the workspace d_ws of ws_bytes.  commit_check
+// then the launches with the workspace d_ws of ws_bytes.  commit_check
 // runs the validation alone and returns the workspace bytes needed.
 fate_status_t commit_check(const fate_dags_t *dags, const fate_state_h *state, const int32_t *d_sel,
                            int32_t sel_stride, size_t *ws_total);

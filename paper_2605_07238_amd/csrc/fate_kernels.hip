@@ -6,16 +6,20 @@
 // capacity fits, and a work-sorted order of the slice's frontier stages (most
 // horizon descendants first, so the lane groups of a wave stay balanced).
 // Each frontier stage v is then handled by one lane group of G lanes (G =
-// next power of two >= D, 4..64); lane d stands for device d.
+// next power of two >= D, 4..64); lane d stands for device d.  A slice with no
+// more stages than lane groups deals its rows to all groups first and has one
+// group per stage add the parts.
 //   1. Lane d evaluates the immediate terms of v on device d (App. A.3):
 //      waiting, switch, transfer from completed parents, colocation, prefix
 //      reuse, and the post-state of d after loading m(v) (Load with eviction
-//      of the smallest-id other models while over capacity; the slot layout
-//      reads it, and the cost terms, from per-block tables built once).
-//   2. Slot 0 of lane d is the single-device candidate {d}; slots 1..3 hold
-//      contiguous windows.  A window's immediate cost is the maximum over its
-//      devices of the per-device time with runtime, transfer and prefix split
-//      k ways, plus the output gather term (cheapest gather target).
+//      of the smallest-id other models while over capacity; up to 32 devices
+//      read it from a per-block table built once, and the slot layout the
+//      cost terms too).
+//   2. Slot 0 of lane d is the single-device candidate {d}; slots 1..3 hold the
+//      windows of 2, 3 and 4 devices that start at d.  A window's immediate
+//      cost is the maximum over its devices of the per-device time with
+//      runtime, transfer and prefix split k ways, plus the output gather term
+//      (cheapest gather target).
 //   3. For each horizon descendant w of v (breadth-first levels 1..H, packed
 //      by the host) lane d' computes B(d') = c_hat(w, d' | s) and the value it
 //      takes once v sits on d' (model loaded, prefix group cached, v's output
@@ -24,7 +28,9 @@
 //      v_max_u32 per step; 32- and 64-lane groups add the other rows' minima
 //      through scalar registers) give the best device outside any window in
 //      O(1); the best device inside a window is a minimum over at most four
-//      lanes.
+//      lanes.  Where coefficients differ, a child of v takes the minimum over
+//      the devices of B plus v's output moved there from the candidate, against
+//      a table of the cheapest coefficients per candidate (at most 32 devices).
 //      min(outside, inside) is w's value under the candidate; it is weighted
 //      by gamma^depth and accumulated in fp64.
 //   This is an exact rearrangement of evaluating c_hat from scratch in the
@@ -34,6 +40,7 @@
 //
 // k_topk: one lane group per frontier stage; k rounds of a group-wide maximum
 // of order-preserving score bits, then of the lowest candidate index holding it.
+// k_topk_lane: one lane per stage, for stages of at most 16 single devices, k <= 4.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
