@@ -298,8 +298,10 @@ fate_status_t fate_pack_state_size(const fate_dags_t *packed, const fate_dag_bat
 
 /* fate_pack_state: validate, build the frontier list (ordered by instance,
  * then stage id) and candidate offsets, copy state and frontier to d_buf on
- * `stream`, gather the completed-parent lists there from the packed DAGs (on
- * the host when those are not in the memory of d_buf's GPU) and synchronise.
+ * `stream` and synchronise.  The completed-parent lists are gathered by a
+ * kernel on `stream` from the packed DAGs where these, d_buf, the stream and
+ * the current device are one GPU and the image is not small (about 512 KB),
+ * else on the host; the image is the same.
  * Errors: as the size query, ESIZE, EHIP. */
 fate_status_t fate_pack_state(const fate_dags_t *packed, const fate_dag_batch_t *dags,
                               const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,

@@ -733,28 +733,37 @@ fate_status_t write_state_device(const fate_dags_t *pk, const fate_state_t *st, 
     return ok ? FATE_OK : FATE_EHIP;
 }
 
-// Whether the packed DAGs are in the memory of the GPU that holds d_buf, so
-// that a kernel may read them there (a handle laid out in host memory is
-// packed on the host).
-bool on_same_gpu(const fate_dags_t *pk, const void *d_buf) {
+// Whether a kernel launched on `stream` may build the lists: the packed DAGs
+// and d_buf are in the memory of one GPU, which is the stream's and the current
+// one.  (A handle laid out in host memory, or a buffer on another GPU than the
+// stream's, is packed on the host: copies reach any GPU's memory, a kernel does
+// not.)
+bool on_stream_gpu(const fate_dags_t *pk, const void *d_buf, void *stream) {
     hipPointerAttribute_t x, y;
     if (pk->N == 0) return false;
     if (hipPointerGetAttributes(&x, pk->records) != hipSuccess || hipPointerGetAttributes(&y, d_buf) != hipSuccess) {
         (void)hipGetLastError();  // host memory that HIP does not know
         return false;
     }
-    return x.type == hipMemoryTypeDevice && y.type == hipMemoryTypeDevice && x.device == y.device;
+    if (x.type != hipMemoryTypeDevice || y.type != hipMemoryTypeDevice || x.device != y.device) return false;
+    int current = -1;
+    hipDevice_t on = -1;
+    if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(reinterpret_cast<hipStream_t>(stream), &on) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return current == y.device && (int)on == y.device;
 }
 
 // Whether the lists of a packed state are gathered on the host: where no kernel
-// may read the DAGs, and for small images, whose one copy costs less than the
+// on the stream may read the DAGs and write d_buf, and for small images, whose one copy costs less than the
 // dozen copies and the launch of the other way (about 100 us; a host gathers
 // and copies some 350 KB in that time).
 constexpr int64_t kSmallImage = 512 * 1024;
-bool lists_on_host(const fate_dags_t *pk, const fate_state_t *st, const void *d_buf) {
+bool lists_on_host(const fate_dags_t *pk, const fate_state_t *st, const void *d_buf, void *stream) {
     if (!pk || !st) return true;
     const int64_t bytes = 16 * pk->E + 12 * pk->N + 8 * (int64_t)pk->B * pk->D * (std::max(0, st->K) + 2);
-    return bytes < kSmallImage || !on_same_gpu(pk, d_buf);
+    return bytes < kSmallImage || !on_stream_gpu(pk, d_buf, stream);
 }
 
 // A packed state's image: sections and kernel, or (lists) the host's image
@@ -912,7 +921,7 @@ fate_status_t fate_pack_state(const fate_dags_t *packed, const fate_dag_batch_t 
                               const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                               void *stream, fate_state_h *out) {
     if (!d_buf || !out) return FATE_EINVAL;
-    const bool lists = lists_on_host(packed, state, d_buf);
+    const bool lists = lists_on_host(packed, state, d_buf, stream);
     StatePlan p;
     fate_status_t st = plan_state(packed, dags, state, max_shard, lists, &p);
     if (st != FATE_OK) return st;
@@ -941,7 +950,7 @@ fate_status_t fate_pack_state_advance(const fate_dags_t *packed, const fate_dag_
                                       const fate_state_t *state, int32_t max_shard, void *d_buf, size_t bytes,
                                       void *stream, fate_state_h *out) {
     if (!d_buf || !out) return FATE_EINVAL;
-    const bool lists = lists_on_host(packed, state, d_buf);
+    const bool lists = lists_on_host(packed, state, d_buf, stream);
     StatePlan p;
     fate_status_t st = plan_state(packed, dags, state, max_shard, lists, &p);
     if (st != FATE_OK) return st;
