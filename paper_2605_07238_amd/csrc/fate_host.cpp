@@ -12,7 +12,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <system_error>
+#include <exception>
 #include <thread>
 #include <vector>
 
@@ -390,13 +390,27 @@ InstScan scan_instance(const fate_dag_batch_t *g, const fate_state_t *st, int D,
 // against some 20 us).
 constexpr int64_t kScanStages = 32768;
 
-// fn(t, first, end) for contiguous ranges of the instances with about equal
+// Ranges that the instances of a batch of N stages are scanned in.
+int scan_ranges(int64_t N) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(fate_host::worker_count(), N / kScanStages));
+}
+
+// fn(t, first, end) for T contiguous ranges of the instances with about equal
 // numbers of stages, one range per thread (the last on the caller's; a range
-// whose thread cannot be started too).
+// whose thread cannot be started too).  What a range throws is thrown here
+// once every thread has ended, the first range's first.
 template <class F>
-void instance_ranges(const fate_dag_batch_t *g, int64_t N, F &&fn) {
-    const int T = (int)std::max<int64_t>(1, std::min<int64_t>(fate_host::worker_count(), N / kScanStages));
+void instance_ranges(const fate_dag_batch_t *g, int64_t N, int T, F &&fn) {
+    std::vector<std::exception_ptr> thrown(T);
     std::vector<std::thread> ts;
+    ts.reserve(T);
+    auto range = [&fn, &thrown](int t, int first, int end) noexcept {
+        try {
+            fn(t, first, end);
+        } catch (...) {
+            thrown[t] = std::current_exception();
+        }
+    };
     int first = 0;
     for (int t = 0; t < T; ++t) {
         const int64_t upto = N * (t + 1) / T;
@@ -404,15 +418,17 @@ void instance_ranges(const fate_dag_batch_t *g, int64_t N, F &&fn) {
         bool started = false;
         if (t + 1 < T) {
             try {
-                ts.emplace_back([&fn, t, first, end] { fn(t, first, end); });
+                ts.emplace_back(range, t, first, end);
                 started = true;
-            } catch (const std::system_error &) {
+            } catch (const std::exception &) {  // no thread, or no memory for one
             }
         }
-        if (!started) fn(t, first, end);
+        if (!started) range(t, first, end);
         first = end;
     }
     for (auto &t : ts) t.join();
+    for (const std::exception_ptr &e : thrown)
+        if (e) std::rethrow_exception(e);
 }
 
 // Validate the state and count its frontier and candidates per instance;
@@ -438,8 +454,9 @@ fate_status_t scan_state(const fate_dags_t *pk, const fate_dag_batch_t *g, const
     for (int b = 0; b < B; ++b)
         if (!std::isfinite(st->t_now[b])) return FATE_EINVAL;
     scan->assign(B, InstScan());
-    if (fronts) fronts->assign(fate_host::worker_count(), {});
-    instance_ranges(g, N, [&](int t, int first, int end) {
+    const int T = scan_ranges(N);
+    if (fronts) fronts->assign(T, {});
+    instance_ranges(g, N, T, [&](int t, int first, int end) {
         std::vector<uint32_t> *front = fronts ? &(*fronts)[t] : nullptr;
         for (int b = first; b < end; ++b) {
             const InstScan r = scan_instance(g, st, D, max_shard, b, front);

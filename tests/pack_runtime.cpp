@@ -7,6 +7,8 @@
 //
 //   pack_runtime devices      which GPUs the packing may launch its kernel on,
 //                             and the image it leaves, against the host layout
+//   pack_runtime memory       an allocation that fails, on the caller's thread or
+//                             on one that validates a part of the batch
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -14,7 +16,9 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <functional>
+#include <new>
 #include <random>
 #include <vector>
 
@@ -112,6 +116,22 @@ int launch_lists(const ListsLaunch &a, void *) {
     return 0;
 }
 }  // namespace fate
+
+namespace {
+
+// ---- allocations that fail -----------------------------------------------------
+
+std::atomic<long> fail_at{-1}, allocated{0};  // fail the allocation of this number (counted from 0)
+
+}  // namespace
+
+void *operator new(size_t n) {
+    if (fail_at.load() >= 0 && allocated.fetch_add(1) == fail_at.load()) throw std::bad_alloc();
+    if (void *p = malloc(n ? n : 1)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 namespace {
 
@@ -234,10 +254,67 @@ void devices() {
     printf("devices ok\n");
 }
 
+// A failed allocation leaves each call by std::bad_alloc, on the caller's
+// thread and with every other thread ended, whichever thread it failed on (or
+// the call does without: a range whose thread cannot be started runs on the
+// caller's); the outputs are as they were, and the next call succeeds.
+void memory() {
+    Batch b(std::vector<int>{40000, 1, 30000, 0, 33000, 20000, 25000}, 11);
+    size_t db = 0, sb = 0;
+    CHECK(fate_pack_dags_size(&b.c, &b.g, 0, &db) == FATE_OK);
+    Buffer dags(db, -1);
+    fate_dags_t pk;
+    CHECK(fate_layout_dags(&b.c, &b.g, 0, dags.data(), db, &pk) == FATE_OK);
+    int64_t nf = 0, nc = 0;
+    CHECK(fate_pack_state_size(&pk, &b.g, &b.st, 4, &sb, &nf, &nc) == FATE_OK);
+    Buffer want(sb, -1), out(sb, -1);
+    fate_state_h h;
+    CHECK(fate_layout_state(&pk, &b.g, &b.st, 4, want.data(), sb, &h) == FATE_OK);
+    const std::vector<uint64_t> before(out.mem);
+    for (int call = 0; call < 2; ++call) {
+        long thrown = 0;
+        for (long n = 0;; ++n) {
+            size_t bytes = 1;
+            int64_t f = 2, c = 3;
+            fate_state_h x;
+            memset(&x, 0x5a, sizeof(x));
+            const fate_state_h x0 = x;
+            bool failed = false;
+            fate_status_t st = FATE_OK;
+            allocated = 0;
+            fail_at = n;
+            try {
+                st = call ? fate_layout_state(&pk, &b.g, &b.st, 4, out.data(), sb, &x)
+                          : fate_pack_state_size(&pk, &b.g, &b.st, 4, &bytes, &f, &c);
+            } catch (const std::bad_alloc &) {
+                failed = true;
+            }
+            fail_at = -1;
+            const bool reached = allocated.load() > n;
+            if (failed) {
+                ++thrown;
+                CHECK(bytes == 1 && f == 2 && c == 3 && memcmp(&x, &x0, sizeof(x)) == 0 && out.mem == before);
+            } else {
+                CHECK(st == FATE_OK);
+                if (call) {
+                    CHECK(memcmp(out.data(), want.data(), sb) == 0);
+                    out.mem = before;
+                } else {
+                    CHECK(bytes == sb && f == nf && c == nc);
+                }
+            }
+            if (!reached) break;  // every allocation of the call has failed once
+        }
+        CHECK(thrown > 0);
+    }
+    printf("memory ok\n");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     if (argc > 1 && !strcmp(argv[1], "devices")) devices();
+    else if (argc > 1 && !strcmp(argv[1], "memory")) memory();
     else return 2;
     return 0;
 }

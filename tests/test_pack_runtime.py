@@ -1,6 +1,6 @@
 """The host half of packing a state on the CPU, against a stand-in for the
 GPU runtime (tests/pack_runtime.cpp): which GPUs it may use for the
-completed-parent lists.  The program defines the HIP calls that the library
+completed-parent lists, and allocations that fail.  The program defines the HIP calls that the library
 makes, so the library under test is the built one."""
 
 import os
@@ -33,3 +33,9 @@ def test_lists_are_built_on_the_gpu_of_the_buffers_only(program):
     device are one GPU; packing onto another GPU than the stream's, or from
     DAGs elsewhere, copies only.  The image is the host layout's either way."""
     _run(program, "devices")
+
+
+def test_a_failed_allocation_reaches_the_caller(program):
+    """Whichever allocation of a call fails, on whichever thread, the call ends
+    with std::bad_alloc on the caller's thread or succeeds; never by aborting."""
+    _run(program, "memory")
