@@ -704,53 +704,62 @@ __global__ __launch_bounds__(64) void k_commit_finish(CommitLaunch a) {
     fill_instance(a, b, F, own.x, c0, sl);
 }
 
-// The completed-parent lists of a state being packed, one thread per stage
-// (blockIdx.x: instance): the holders and sizes of a pending stage's
-// completed parents, in parent order, then zeros in the rest of its parent
-// slots; all zeros for other stages.  The lists are most of the image (8 of
-// 11.3 MB for 1,024 layered instances of 200 stages), which the host gathered
-// and copied before: with the validation on several threads and the caller's
-// arrays copied as they are, a state packed, scored and planned 3.66 -> 1.01 ms.
-// Bound by the host's validation and the copies around it.
+// The completed-parent lists of a state being packed, one thread per flat
+// stage, whatever instances the stages fall into: the holders and sizes of a
+// pending stage's completed parents, in parent order, then zeros in the rest
+// of its parent slots; all zeros for other stages.  A planning state's finish
+// times need the stage's instance, which a search of the offsets finds.  The
+// lists are most of the image (8 of 11.3 MB for 1,024 layered instances of 200
+// stages), which the host gathered and copied before: with the validation on
+// several threads and the caller's arrays copied as they are, a state packed,
+// scored and planned 3.66 -> 1.01 ms.  Bound by the host's validation and the
+// copies around it.
 __global__ __launch_bounds__(256) void k_state_lists(ListsLaunch a) {
-    const int b = blockIdx.x;
-    const int64_t base = a.stage_off[b], end = a.stage_off[b + 1];
-    const float tn = a.tnow[b];
-    for (int64_t s = base + (int64_t)blockIdx.y * 256 + threadIdx.x; s < end; s += (int64_t)gridDim.y * 256) {
-        const StageRec r = a.rec[s];
-        const bool list = a.done_n[s] != 0u;
-        uint32_t n = 0;
-        DoneParent zero;
-        zero.holders = 0ull;
-        zero.sigma = 0.0f;
-        zero.pad = 0u;
-        for (uint32_t q0 = 0; list && q0 < r.npar; q0 += kParBatch) {  // the batch's loads are issued together
-            uint32_t u[kParBatch];
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s >= a.N) return;
+    const StageRec r = a.rec[s];
+    const bool list = a.done_n[s] != 0u;
+    uint32_t n = 0;
+    DoneParent zero;
+    zero.holders = 0ull;
+    zero.sigma = 0.0f;
+    zero.pad = 0u;
+    for (uint32_t q0 = 0; list && q0 < r.npar; q0 += kParBatch) {  // the batch's loads are issued together
+        uint32_t u[kParBatch];
 #pragma unroll
-            for (int j = 0; j < kParBatch; ++j) u[j] = a.par_idx[r.par_begin + min(q0 + (uint32_t)j, (uint32_t)r.npar - 1u)];
-            DoneParent e[kParBatch];
+        for (int j = 0; j < kParBatch; ++j) u[j] = a.par_idx[r.par_begin + min(q0 + (uint32_t)j, (uint32_t)r.npar - 1u)];
+        DoneParent e[kParBatch];
 #pragma unroll
-            for (int j = 0; j < kParBatch; ++j) {
-                e[j].holders = a.holders[u[j]];
-                e[j].sigma = a.rec[u[j]].sigma;
-                e[j].pad = 0u;
-            }
-#pragma unroll
-            for (int j = 0; j < kParBatch; ++j)
-                if (q0 + j < r.npar && e[j].holders != 0ull) a.done[r.par_begin + n++] = e[j];
+        for (int j = 0; j < kParBatch; ++j) {
+            e[j].holders = a.holders[u[j]];
+            e[j].sigma = a.rec[u[j]].sigma;
+            e[j].pad = 0u;
         }
-        for (uint32_t q = n; q < r.npar; ++q) a.done[r.par_begin + q] = zero;
-        a.done_n[s] = n;
-        if (a.finish) a.finish[s] = a.holders[s] != 0ull ? tn : 0.0f;
+#pragma unroll
+        for (int j = 0; j < kParBatch; ++j)
+            if (q0 + j < r.npar && e[j].holders != 0ull) a.done[r.par_begin + n++] = e[j];
     }
+    for (uint32_t q = n; q < r.npar; ++q) a.done[r.par_begin + q] = zero;
+    a.done_n[s] = n;
+    if (!a.finish) return;
+    float f = 0.0f;
+    if (a.holders[s] != 0ull) {
+        int lo = 0, hi = a.B;  // the last instance that begins at s or before
+        while (hi - lo > 1) {
+            const int mid = lo + (hi - lo) / 2;
+            if (a.stage_off[mid] <= s) lo = mid;
+            else hi = mid;
+        }
+        f = a.tnow[lo];
+    }
+    a.finish[s] = f;
 }
 
 }  // namespace
 
 int launch_lists(const ListsLaunch &a, void *stream) {
-    if (a.B <= 0 || a.max_stages <= 0) return 0;
-    const int64_t chunks = (a.max_stages + 255) / 256;
-    const dim3 grid((unsigned)a.B, (unsigned)(chunks < 1024 ? chunks : 1024));
+    if (a.N <= 0) return 0;
+    const dim3 grid((unsigned)((a.N + 255) / 256));  // fewer than 2^28 stages
     hipLaunchKernelGGL(k_state_lists, grid, dim3(256), 0, reinterpret_cast<hipStream_t>(stream), a);
     return (int)hipGetLastError();
 }

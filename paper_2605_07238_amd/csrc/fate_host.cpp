@@ -742,8 +742,8 @@ fate_status_t write_state_device(const fate_dags_t *pk, const fate_state_t *st, 
     a.done_n = reinterpret_cast<uint32_t *>(d + L.done_n);
     a.done = reinterpret_cast<fate::DoneParent *>(d + L.done);
     a.finish = advance ? reinterpret_cast<float *>(d + L.finish) : nullptr;
+    a.N = pk->N;
     a.B = B;
-    a.max_stages = pk->max_stages;
     ok = ok && fate::launch_lists(a, stream) == 0;
     // also after a failure: nothing may still read the caller's arrays or the plan
     ok = hipStreamSynchronize(s) == hipSuccess && ok;

@@ -241,8 +241,8 @@ struct ListsLaunch {
     uint32_t *done_n;
     DoneParent *done;
     float *finish;  // planning state: planned finish of the completed stages, or null
+    int64_t N;
     int32_t B;
-    int64_t max_stages;
 };
 int launch_lists(const ListsLaunch &a, void *stream);
 

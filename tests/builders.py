@@ -48,3 +48,36 @@ def from_spec(spec: dict, H: int = 1, params: dict | None = None) -> synth.Workl
     if params:
         w.params.update(params)
     return w
+
+
+def random_batch(sizes, seed: int, D: int = 5, M: int = 3, K: int = 2, fan: int = 3) -> synth.Workload:
+    """Instances of the given numbers of stages (0 among them), each stage with
+    up to `fan` parents among the 300 before it; a random prefix of up to half
+    of an instance is completed, and some of its frontier is running."""
+    rng = np.random.default_rng(seed)
+    n = np.array(sizes)
+    B = len(n)
+    stage_off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    N = int(stage_off[-1])
+    base = np.repeat(stage_off[:-1], n)
+    local = np.arange(N) - base
+    far = np.unique(np.geomspace(1, 300, fan + 1).astype(int))  # a parent from each span of distances
+    back = np.stack([rng.integers(lo, hi, N) for lo, hi in zip(far[:-1], far[1:])][::-1], 1)
+    has = (back <= local[:, None]) & (rng.random(back.shape) < 0.6)
+    par, npar = (local[:, None] - back)[has].astype(np.int32), has.sum(1)
+    child = np.repeat(np.arange(N), npar)
+    done = local < np.repeat(rng.integers(0, n // 2 + 1), n)
+    status = done.astype(np.uint8)
+    left = np.bincount(child, weights=~done[par + base[child]], minlength=N) if len(par) else np.zeros(N)
+    status[~done & (left == 0) & (rng.random(N) < 0.3)] = 2
+    return synth.Workload(
+        name="random", D=D, M=M, K=K, H=0, max_shard=3, stage_off=stage_off,
+        par_off=np.concatenate([[0], np.cumsum(npar)]).astype(np.int64), par_idx=par,
+        model=rng.integers(0, M, N).astype(np.int32), elig=np.full(N, (1 << D) - 1, np.uint64),
+        shard_max=rng.integers(1, 4, N).astype(np.int32), prefix_hash=rng.integers(0, 5, N).astype(np.uint64),
+        prefix_tokens=np.ones(N, np.float32), out_bytes=rng.integers(1, 1000, N).astype(np.float32),
+        exec=np.ones((M, D), np.float32), switch_s=np.ones((M, D), np.float32), weight_bytes=np.full(M, 10, np.int64),
+        cap_bytes=np.full(D, 25, np.int64), beta=np.full((D, D), 1e-9, np.float32),
+        resident=rng.integers(0, 8, (B, D)).astype(np.uint64), prefix_cache=rng.integers(0, 5, (B, D, K)).astype(np.uint64),
+        holders=np.where(done, rng.integers(1, 1 << D, N), 0).astype(np.uint64), status=status,
+        tau_free=rng.random((B, D)).astype(np.float32), t_now=rng.random(B).astype(np.float32))

@@ -9,6 +9,8 @@ completed-parent lists (against the host packer run on the oracle's new
 state), and the next step's scores (within the scoring tolerance).
 """
 
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -431,6 +433,55 @@ def test_state_image_equals_the_host_layout(name, advance):
         img, h, _ = fate.fate_layout_state(hd, w)
         assert np.array_equal(got[:len(img)], img)
     assert (st.n_frontier, st.n_cand, st.handle.n_slices) == (st2.n_frontier, st2.n_cand, st2.handle.n_slices)
+
+
+@pytest.mark.parametrize("advance", [False, True], ids=["plain", "planning"])
+@pytest.mark.parametrize("name,make", [
+    ("ones-and-empties", lambda: builders.random_batch([1, 0, 1, 1, 0, 0, 2] * 4000, 1, K=2)),
+    ("no-slots", lambda: builders.random_batch([0, 7, 300, 1, 40] * 200, 2, D=3, K=0)),
+    ("parents", lambda: builders.random_batch([0, 255, 256, 257, 5000, 1], 3, fan=24)),  # eight to a batch of loads
+], ids=lambda x: x if isinstance(x, str) else "")
+def test_state_image_of_edge_shapes(name, make, advance):
+    """As above for single and empty instances, no prefix slots and stages of
+    more than eight parents, in batches that are large enough for the kernel
+    (the small ones above are gathered on the host)."""
+    import torch
+    w = make()
+    assert 16 * len(w.par_idx) + 12 * w.N + 8 * w.B * w.D * (w.K + 2) >= 512 * 1024
+    print("[commit] state image", name, advance, flush=True)
+    pk = fate.fate_pack_dags(w)
+    hbuf, hd, hi = fate.fate_layout_dags(w)
+    host = fate.PackedDags(pk.buf, hd, hi)  # no kernel may read this handle's memory
+    st, want = fate.fate_pack_state(pk, w, advance=advance), fate.fate_pack_state(host, w, advance=advance)
+    assert torch.equal(st.buf, want.buf)
+
+
+def test_state_image_of_very_many_instances():
+    """More instances than a launch of a workgroup each can hold (2^24), nearly
+    all of them empty, as a plain and as a planning state."""
+    import torch
+    B = (1 << 24) + 3
+    n = np.zeros(B, np.int64)
+    n[[0, 1, (1 << 23) - 1, 1 << 23, (1 << 23) + 1, (1 << 24) - 1, 1 << 24, B - 1]] = [5, 9, 7, 12, 3, 1, 600, 4]
+    stage_off = np.concatenate([[0], np.cumsum(n)])
+    N = int(stage_off[-1])
+    local = np.arange(N) - np.repeat(stage_off[:-1], n)
+    w = synth.make_random_small(1, B=1, n=N, D=2, M=2, K=0, H=0)
+    has = local > 0  # a chain per instance, its first half completed
+    done = 2 * local < np.repeat(n, n)
+    w = dataclasses.replace(
+        w, stage_off=stage_off, par_off=np.concatenate([[0], np.cumsum(has)]).astype(np.int64),
+        par_idx=(local[has] - 1).astype(np.int32), holders=np.where(done, 2, 0).astype(np.uint64), status=done.astype(np.uint8),
+        resident=np.zeros((B, 2), np.uint64), prefix_cache=np.zeros((B, 2, 0), np.uint64),
+        tau_free=np.zeros((B, 2), np.float32), t_now=np.zeros(B, np.float32))
+    w.t_now[:] = np.arange(B) % 1000
+    print("[commit] state image of", B, "instances", flush=True)
+    pk = fate.fate_pack_dags(w)
+    hbuf, hd, hi = fate.fate_layout_dags(w)
+    host = fate.PackedDags(pk.buf, hd, hi)
+    for advance in (False, True):
+        st, want = fate.fate_pack_state(pk, w, advance=advance), fate.fate_pack_state(host, w, advance=advance)
+        assert torch.equal(st.buf, want.buf), advance
 
 
 @pytest.mark.parametrize("B", [1, 63, 64, 65, 1024, 1025])

@@ -10,40 +10,12 @@ import dataclasses
 import numpy as np
 import pytest
 
-from paper_2605_07238_amd import fate, synth
+import builders
+from paper_2605_07238_amd import fate
 
-D, M, K = 5, 3, 2
+D = 5
 # a range border falls on an empty instance, inside the largest one and between two
 SIZES = [0, 20000, 0, 12768, 0, 1, 70000, 3, 0, 0, 30000, 2768, 40000, 1, 17000, 0]
-
-
-def _batch(sizes, seed):
-    """Instances whose stages have up to three near parents; a random prefix
-    of each is completed, some of its frontier is running."""
-    rng = np.random.default_rng(seed)
-    n = np.array(sizes)
-    stage_off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
-    N, B = int(stage_off[-1]), len(sizes)
-    local = np.arange(N) - np.repeat(stage_off[:-1], n)
-    back = np.stack([rng.integers(1, 5, N), rng.integers(5, 30, N), rng.integers(30, 300, N)], 1)[:, ::-1]
-    has = (back <= local[:, None]) & (rng.random((N, 3)) < 0.6)
-    par = (local[:, None] - back)[has].astype(np.int32)
-    child = np.repeat(np.arange(N), has.sum(1))
-    done = local < np.repeat(rng.integers(0, n // 2 + 1), n)
-    status = np.where(done, 1, 0).astype(np.uint8)
-    left = np.bincount(child, weights=~done[par + np.repeat(stage_off[:-1], n)[child]], minlength=N)
-    status[(~done) & (left == 0) & (rng.random(N) < 0.3)] = 2
-    return synth.Workload(
-        name="ranges", D=D, M=M, K=K, H=0, max_shard=3, stage_off=stage_off,
-        par_off=np.concatenate([[0], np.cumsum(has.sum(1))]).astype(np.int64), par_idx=par,
-        model=rng.integers(0, M, N).astype(np.int32), elig=np.full(N, (1 << D) - 1, np.uint64),
-        shard_max=rng.integers(1, 4, N).astype(np.int32), prefix_hash=rng.integers(0, 5, N).astype(np.uint64),
-        prefix_tokens=np.ones(N, np.float32), out_bytes=rng.integers(1, 1000, N).astype(np.float32),
-        exec=np.ones((M, D), np.float32), switch_s=np.ones((M, D), np.float32), weight_bytes=np.full(M, 10, np.int64),
-        cap_bytes=np.full(D, 25, np.int64), beta=np.full((D, D), 1e-9, np.float32),
-        resident=rng.integers(0, 8, (B, D)).astype(np.uint64), prefix_cache=rng.integers(0, 5, (B, D, K)).astype(np.uint64),
-        holders=np.where(done, rng.integers(1, 1 << D, N), 0).astype(np.uint64), status=status,
-        tau_free=rng.random((B, D)).astype(np.float32), t_now=rng.random(B).astype(np.float32))
 
 
 def _piece(w, b0, b1):
@@ -72,7 +44,7 @@ def _sections(w):
 
 
 def test_ranges_give_the_pieces_image():
-    w = _batch(SIZES, 1)
+    w = builders.random_batch(SIZES, 1, D=D)
     assert w.N >= 4 * 32768
     got = _sections(w)
     F = C0 = 0
@@ -128,7 +100,7 @@ def _where(w, b):
 def test_first_error_in_stage_order(first, second):
     """Two errors in different ranges (or one), either kind first; the state
     calls and the host layout return the earlier one's status."""
-    w = _batch(SIZES, 2)
+    w = builders.random_batch(SIZES, 2, D=D)
     _, h, _ = fate.fate_layout_dags(w)
     lib = fate.load()
     kinds = ("status", "device", "early", "parent")
