@@ -2313,14 +2313,18 @@ struct alignas(16) StageR4 {
 static_assert(sizeof(StageR4) == 80, "StageR4");
 
 constexpr int kRows4Devs = 64;                       // devices a row can span
-// Floats per model row of each of the two cost tables, (exec + switch term) and
-// the signed switch magnitude: a row reads the first before its minimum and the
-// second after it, sixteen bytes per lane and load; the four floats more start
-// rows of different models on different banks.  As one table of pairs the reads
-// were strided eight-byte ones, and the power-law batch took 74.1 us (58.2).
+// Floats per model row of the cost table: (exec + switch term) of every device,
+// then the signed switch magnitudes, then four more, which start rows of
+// different models on different banks.  A row reads the first half before its
+// minimum and the second after it, sixteen bytes per lane and load.  As pairs
+// the reads were strided eight-byte ones, and the power-law batch took 74.1 us
+// (58.2).  Padding each half would cost 16 bytes a model, and with them the
+// fit: 26 models with more than 1,024 prefix slots over all devices just fit (the
+// general kernel takes 260 us on 256 power-law instances of 64 devices there,
+// this one 59).
 // (k_rows keeps the pairs: whole float4s there cost it five spilled registers,
 // 380 against 394 us on a 14-set sweep.)
-constexpr int kRows4Stride = kRows4Devs + 4;
+constexpr int kRows4Stride = 2 * kRows4Devs + 4;
 
 struct Rows4Plan {
     uint32_t pkey, pmask, rho, cap, wt, fits, wait, gpow, rtab, flf, stages, tasks, part, misc, total;
@@ -2343,7 +2347,7 @@ __host__ __device__ inline Rows4Plan rows4_plan(int D, int K, int M, int blk) {
     q.wait = o; o += 4 * kRows4Devs;
     q.gpow = o; o += 4 * 16;
     o = (o + 15u) & ~15u;
-    q.rtab = o; o += 8 * (uint32_t)(M * kRows4Stride);
+    q.rtab = o; o += 4 * (uint32_t)(M * kRows4Stride);
     o = (o + 7u) & ~7u;
     q.flf = o; o += 8 * (uint32_t)(M * M);
     o = (o + 15u) & ~15u;
@@ -2397,7 +2401,7 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
     uint64_t *fits = reinterpret_cast<uint64_t *>(sb + plan.fits);
     float *wait = reinterpret_cast<float *>(sb + plan.wait);
     float *gpow = reinterpret_cast<float *>(sb + plan.gpow);
-    float *rtab = reinterpret_cast<float *>(sb + plan.rtab), *rks = rtab + M * CS;
+    float *rtab = reinterpret_cast<float *>(sb + plan.rtab), *rks = rtab + kRows4Devs;
     uint64_t *flf = reinterpret_cast<uint64_t *>(sb + plan.flf);  // per (m(v), m(w)): devices where Load flips m(w)
     StageR4 *stg = reinterpret_cast<StageR4 *>(sb + plan.stages);
     uint32_t *tasks = reinterpret_cast<uint32_t *>(sb + plan.tasks);
@@ -2612,7 +2616,7 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
                 const float pfp = lam_p * ps.kpf * rw.tokens;
                 const float cw = lam_c * fast_rcp((float)rw.npar);  // a descendant has at least one parent
                 const uint32_t flip = (uint32_t)((flf[mrow + mw] >> dq) & 0xffffull);
-                const float *crow = rtab + mw * CS + dq, *krow = rks + mw * CS + dq;
+                const float *crow = rtab + mw * CS + dq, *krow = crow + kRows4Devs;
                 // B without the completed parents: cost with the switch term, less the prefix benefit
                 float B[ND];
 #pragma unroll

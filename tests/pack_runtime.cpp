@@ -7,6 +7,7 @@
 //
 //   pack_runtime devices      which GPUs the packing may launch its kernel on,
 //                             and the image it leaves, against the host layout
+//   pack_runtime shapes       up to how many models the row kernels take a cluster
 //   pack_runtime memory       an allocation that fails, on the caller's thread or
 //                             on one that validates a part of the batch
 #include <hip/hip_runtime.h>
@@ -310,11 +311,26 @@ void memory() {
     printf("memory ok\n");
 }
 
+// The models up to which a row kernel's tables fit, by devices and prefix slots
+// (a shape past them takes the general kernel, several times slower).
+void shapes() {
+    const int most[][3] = {{1, 32, 32}, {16, 0, 32}, {16, 32, 32}, {17, 16, 64}, {32, 16, 64}, {32, 32, 53},
+                           {33, 31, 53}, {33, 32, 26}, {48, 32, 26}, {64, 16, 53}, {64, 17, 26}, {64, 32, 26}};
+    for (const auto &x : most) {
+        int m = 0;
+        while (m < FATE_MAX_MODELS && fate::rows_kernel_fits(x[0], x[1], m + 1)) ++m;
+        if (m != x[2]) printf("%d devices, %d slots: %d models\n", x[0], x[1], m);
+        CHECK(m == x[2]);
+    }
+    printf("shapes ok\n");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     if (argc > 1 && !strcmp(argv[1], "devices")) devices();
     else if (argc > 1 && !strcmp(argv[1], "memory")) memory();
+    else if (argc > 1 && !strcmp(argv[1], "shapes")) shapes();
     else return 2;
     return 0;
 }

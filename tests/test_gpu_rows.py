@@ -116,6 +116,14 @@ def test_rows4_topk(k):
     check_against_oracle(w, run_gpu(w, k=k), k=k)
 
 
+@pytest.mark.parametrize("D,K,M", [(33, 32, 26), (64, 17, 26), (64, 32, 26), (64, 32, 27), (64, 16, 53), (64, 16, 54)])
+def test_rows4_most_models(D, K, M):
+    """Clusters whose tables just fit k_rows4, and the first that go to the general kernel."""
+    w = _rows_workload(90 + M, D=D, M=M, K=K, n=60)
+    print("[rows4] most models", D, K, M, flush=True)
+    check_against_oracle(w, run_gpu(w, k=4), k=4)
+
+
 @pytest.mark.parametrize("D,M", [(4, 3), (7, 5), (16, 12), (24, 6), (64, 9)])
 def test_rows_variants(D, M):
     """The same-model weight and windows switched off on frontiers without

@@ -1,6 +1,7 @@
 """The host half of packing a state on the CPU, against a stand-in for the
 GPU runtime (tests/pack_runtime.cpp): which GPUs it may use for the
-completed-parent lists, and allocations that fail.  The program defines the HIP calls that the library
+completed-parent lists, which clusters the row kernels take, and allocations
+that fail.  The program defines the HIP calls that the library
 makes, so the library under test is the built one."""
 
 import os
@@ -39,3 +40,8 @@ def test_a_failed_allocation_reaches_the_caller(program):
     """Whichever allocation of a call fails, on whichever thread, the call ends
     with std::bad_alloc on the caller's thread or succeeds; never by aborting."""
     _run(program, "memory")
+
+
+def test_clusters_that_the_row_kernels_take(program):
+    """The row kernels' tables grow to just what fits the LDS, not past it."""
+    _run(program, "shapes")
