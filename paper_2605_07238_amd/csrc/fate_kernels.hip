@@ -2527,7 +2527,9 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             // shorter tail task; the tail tasks ordered by length, longest
             // first (ties by stage), so that the quads of a wave run the same
             // number of rows
-            const int i0 = 2 * tid, i1 = 2 * tid + 1;
+            int pt = tid;  // opaque, so that addresses from it are not kept in registers over the chunk loop
+            asm volatile("" : "+v"(pt));
+            const int i0 = 2 * pt, i1 = 2 * pt + 1;
             const uint32_t n0 = i0 < nC ? stg[i0].n : 0u, n1 = i1 < nC ? stg[i1].n : 0u;
             uint32_t R = 0, S = 0;
             (void)wave_exscan_u32(n0 + n1, R);
@@ -2548,7 +2550,7 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             uint32_t *bkt = reinterpret_cast<uint32_t *>(partf);  // scratch until the rows write their sums
             constexpr uint32_t kBuckets = 32;
             auto bucket = [&](uint32_t len) { return len >= kBuckets ? kBuckets - 1u : len; };
-            if (tid < (int)kBuckets) bkt[tid] = 0u;
+            if (pt < (int)kBuckets) bkt[pt] = 0u;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -2557,13 +2559,13 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const uint32_t cb = tid < (int)kBuckets ? bkt[kBuckets - 1u - (uint32_t)tid] : 0u;  // longest first
+            const uint32_t cb = pt < (int)kBuckets ? bkt[kBuckets - 1u - (uint32_t)pt] : 0u;  // longest first
             uint32_t ntail = 0;
             const uint32_t start = nfull + wave_exscan_u32(cb, ntail);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (tid < (int)kBuckets) bkt[kBuckets - 1u - (uint32_t)tid] = start;
+            if (pt < (int)kBuckets) bkt[kBuckets - 1u - (uint32_t)pt] = start;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
