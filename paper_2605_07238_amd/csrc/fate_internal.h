@@ -90,6 +90,7 @@ struct ScoreLaunch {
     int32_t topo;  // descendant lists by topological level (FATE_LEVELS_TOPO)
     int32_t Hpack;      // horizon the descendant lists were packed with
     int32_t singles;    // every frontier stage has only single-device candidates
+    int64_t max_stages; // stages of the largest instance
     int32_t nsets;
     ParamSet ps[kMaxSets];
     int32_t set_of[kMaxSets];  // grid row y scores parameter set set_of[y] (its place in the output)
@@ -153,7 +154,7 @@ struct CommitLaunch {
 bool rows_kernel_fits(int D, int K, int M);
 
 // Whether scoring on this batch takes a row kernel (k_rows, k_rows4) for
-// parameter sets that sum over the levels: single-device candidates only, uniform
+// parameter sets without a variant: single-device candidates only, uniform
 // beta, hop levels, and tables that fit.  Its scoring slices then go unused,
 // and the packer and the commit leave them in instance order; otherwise they
 // follow the dispatch order (largest frontiers first).

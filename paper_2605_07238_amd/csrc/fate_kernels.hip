@@ -1774,7 +1774,8 @@ __global__ __launch_bounds__(kBlock) void k_topk_lane(TopkLaunch a) {
 
 // ---- k_rows: one horizon row per lane ---------------------------------------
 // For frontiers whose stages have single-device candidates only, with a
-// uniform off-diagonal beta, D <= 16, hop levels and their sum.  One workgroup
+// uniform off-diagonal beta, D <= 16 and no scoring variant (some in short
+// runs).  One workgroup
 // per instance: it stages the instance's tables in LDS once (prefix-group
 // table, per-(model, device) cost terms, and, per pair of models, the devices
 // where loading the first flips the residency of the second), then takes the
@@ -1812,6 +1813,14 @@ struct alignas(16) StageR {
 static_assert(sizeof(StageR) == 64, "StageR");
 
 constexpr int kRowsChunk = 128;  // frontier stages per chunk of an instance
+
+// Short runs: at most this many of a task's rows in one fp32 sum, as in the slot
+// layout's batches; a chunk then takes as many stages as have short_rows rows
+// (16 for each task slot that the tails of 128 stages leave).
+constexpr int kShortRun = 16;
+constexpr int short_rows(int blk) { return kShortRun * (blk - kRowsChunk); }
+// Rows of the largest stage that still gives tasks of kShortRun rows.
+constexpr int short_most(int blk) { return kShortRun * (blk - 1); }
 
 // floats per model row of the rows' cost table: (exec + switch term, switch
 // magnitude) per device, plus four (rows of different models start on
@@ -1862,6 +1871,9 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
     static_assert(BLK >= kRowsChunk && BLK % 64 == 0, "one thread per stage of a chunk");
     const int b = (int)a.order[blockIdx.x];  // largest frontiers first: the last workgroups to start are short
     const ParamSet ps = a.ps[blockIdx.y];
+    // sets with a variant that the row kernel takes (9 to 16 devices) keep runs short
+    constexpr bool kShort = ND == 16;
+    const bool short_run = kShort && (ps.lam_m != 0.0f || ps.flags != 0);
     float *const scores = a.scores + (int64_t)a.set_of[blockIdx.y] * a.score_stride;
     extern __shared__ uint64_t smem[];
     uint8_t *sb = reinterpret_cast<uint8_t *>(smem);
@@ -1911,7 +1923,8 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             const int j = m * D + d;
             const float ks = ps.lam_s * a.ksw[j];
             const bool res = bit(a.resident[(int64_t)b * D + d], m);
-            const float swo = res ? 0.0f - ps.lam_m : ks;  // the same-model weight beside the switch time
+            const float lam_m = kShort ? ps.lam_m : 0.0f;  // the same-model weight, beside the switch time
+            const float swo = res ? 0.0f - lam_m : ks;
             sw0 = a.exec[j] + swo;
             CostS c;
             c.sw0 = sw0;
@@ -1924,7 +1937,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             // sign of the change a flip of the residency makes: up where m is
             // resident now (evicted), down where it is not (loaded)
             if (!bit(a.fits[m], d)) sw0 = inf_f();
-            sks = res ? ks + ps.lam_m : -(ks + ps.lam_m);
+            sks = res ? ks + lam_m : -(ks + lam_m);
         }
         rtab[m * CS + 2 * d] = sw0;  // devices past D: never feasible
         rtab[m * CS + 2 * d + 1] = sks;
@@ -1973,8 +1986,8 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
     const int dl = live ? lane : D - 1;
     const bool lane_rank = a.topk > 0 && a.topk <= kLaneTopk;
 
-    for (int c0 = 0; c0 < nFi; c0 += kRowsChunk) {  // uniform: chunks of the instance's frontier
-        const int nC = min(kRowsChunk, nFi - c0);
+    for (int c0 = 0, step = kRowsChunk; c0 < nFi; c0 += step) {  // uniform: chunks of the instance's frontier
+        int nC = min(kRowsChunk, nFi - c0);
         const int64_t fc = lo + c0;  // frontier slot of the chunk's first stage
         if (tid < nC) {  // stage records, descendant ranges, v's first completed parent
             const uint32_t v = a.frontier[2 * (fc + tid)];
@@ -2022,8 +2035,16 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             // first (ties by stage), so that the lanes of a wave run the same
             // number of rows
             const int i0 = 2 * tid, i1 = 2 * tid + 1;
-            const uint32_t n0 = i0 < nC ? stg[i0].n : 0u, n1 = i1 < nC ? stg[i1].n : 0u;
+            uint32_t n0 = i0 < nC ? stg[i0].n : 0u, n1 = i1 < nC ? stg[i1].n : 0u;
             uint32_t R = 0, S = 0;
+            if (short_run) {  // the first stages of at most short_rows(BLK) rows, but one at least
+                const uint32_t before = wave_exscan_u32(n0 + n1, R), most = (uint32_t)short_rows(BLK);
+                const bool in0 = i0 < nC && (i0 == 0 || before + n0 <= most), in1 = i1 < nC && before + n0 + n1 <= most;
+                nC = __popcll(__ballot(in0)) + __popcll(__ballot(in1));
+                n0 = in0 ? n0 : 0u;
+                n1 = in1 ? n1 : 0u;
+                if (tid == 0) misc[4] = (uint32_t)nC;
+            }
             (void)wave_exscan_u32(n0 + n1, R);
             (void)wave_exscan_u32((n0 ? 1u : 0u) + (n1 ? 1u : 0u), S);
             // binary search between ceil(R / cap), below which the full tasks
@@ -2092,6 +2113,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
         __syncthreads();
         const int ntask = (int)misc[2];
         const uint32_t Lr = misc[3];
+        if (short_run) step = nC = (int)misc[4];
 
         // ---- rows
         for (int t = tid; t < ntask; t += BLK) {
@@ -2285,7 +2307,7 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
                 lane_topk(x, a.topk, a.tk_idx + f * a.topk, a.tk_val + f * a.topk);
             }
         }
-        if (c0 + kRowsChunk < nFi) __syncthreads();  // uniform: the next chunk reuses the stage slots and task sums
+        if (c0 + step < nFi) __syncthreads();  // uniform: the next chunk reuses the stage slots and task sums
     }
 }
 
@@ -2434,11 +2456,11 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
             const int j = m * D + d;
             const float ks = ps.lam_s * a.ksw[j];
             const bool res = bit(a.resident[(int64_t)b * D + d], m);
-            sw0 = a.exec[j] + (res ? 0.0f - ps.lam_m : ks);  // the same-model weight beside the switch time
+            sw0 = a.exec[j] + (res ? 0.0f : ks);
             // +infinity where the model does not fit; the magnitude signed by
             // the change a flip of the residency makes (up where resident now)
             if (!bit(a.fits[m], d)) sw0 = inf_f();
-            sks = res ? ks + ps.lam_m : -(ks + ps.lam_m);
+            sks = res ? ks : -ks;
         }
         rtab[m * CS + d] = sw0;  // devices past D: never feasible
         rks[m * CS + d] = sks;
@@ -2746,10 +2768,8 @@ __global__ __launch_bounds__(BLK) void k_rows4(ScoreLaunch a) {
                 }
             }
             // the switch term where m(v) is not resident (the row table's
-            // magnitude is negative there, and holds the same-model weight too)
-            const float swo = bit(rho[dl], s.model) ? 0.0f - ps.lam_m
-                              : ps.lam_m == 0.0f    ? -rks[s.model * CS + dl]
-                                                    : ps.lam_s * a.ksw[s.model * D + dl];
+            // magnitude is negative there)
+            const float swo = bit(rho[dl], s.model) ? 0.0f : -rks[s.model * CS + dl];
             const float ex = a.exec[s.model * D + dl];
             const float pf_v = ((s.pfm >> dl) & 1ull) ? ps.kpf * s.tokens : 0.0f;
             const float colo = s.npar ? cnt * fast_rcp((float)s.npar) : 0.0f;
@@ -2849,7 +2869,7 @@ constexpr int kRowsBlock = 256;
 constexpr int kRows4Block = 1024;
 
 // The row kernels take frontiers with single-device candidates only, uniform
-// beta, hop levels and parameter sets that sum over the levels: k_rows up
+// beta, hop levels and parameter sets without a scoring variant: k_rows up
 // to 16 devices and 32 models, k_rows4 up to 64 devices and 64 models, when
 // their LDS fits.
 bool rows_kernel_fits(int D, int K, int M) {
@@ -2886,16 +2906,24 @@ template <bool UNI>
 static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStream_t s) {
     ScoreLaunch a = a0;
     if (UNI && rows_fit(a0)) {
-        // each parameter set goes where a launch of that set alone would go: the
-        // row kernels take all but the mean per level (its weights are per
-        // descendant entry), which goes below.  There are no windows to turn
-        // off here, and the same-model weight is part of the switch table: on
-        // 1,024 fork-join instances such a set took 104 us in k_score, 27 in k_rows
+        // Each parameter set goes where a launch of that set alone would go:
+        // sets without a variant to the row kernels, the others to the general
+        // kernel, which sums in more bits: every row in fp64 (and picks the
+        // same-model weight or the switch time, where the row tables add and
+        // subtract both), or, in the slot layout of 9 to 16 devices, sixteen
+        // rows in fp32 from tables like the row kernel's.  There a set that
+        // only adds the weight or turns windows off (there are none here)
+        // takes the row kernel, in runs of sixteen rows, as long as the
+        // largest stage's rows fit them: 1,024 fork-join instances, 104 us in
+        // k_score, 27 in k_rows.
+        const bool short_fits = a0.D > 8 && a0.D <= 16 && a0.max_stages - 1 <= short_most(kRowsBlock);
         ScoreLaunch r = a0;
         r.nsets = a.nsets = 0;
         for (int p = 0; p < a0.nsets; ++p) {
-            ScoreLaunch &x = (a0.ps[p].flags & FATE_MEAN_PER_LEVEL) != 0 ? a : r;
-            x.ps[x.nsets] = a0.ps[p];
+            const ParamSet &ps = a0.ps[p];
+            const bool plain = ps.lam_m == 0.0f && ps.flags == 0;
+            ScoreLaunch &x = plain || (short_fits && !(ps.flags & FATE_MEAN_PER_LEVEL)) ? r : a;
+            x.ps[x.nsets] = ps;
             x.set_of[x.nsets] = a0.set_of[p];
             ++x.nsets;
         }

@@ -8,11 +8,14 @@ top-k above the one-lane ranking (the group ranks then); k_rows4, one row per
 four lanes, for 17 to 64 devices (quads whose upper lanes hold no device,
 the largest tables, several chunks, dense parents, top-k up to 64)."""
 
+import dataclasses
+
 import numpy as np
 import pytest
 
 from gpu_util import check_against_oracle, run_gpu
-from paper_2605_07238_amd import synth
+from oracle import oracle
+from paper_2605_07238_amd import fate, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -127,7 +130,7 @@ def test_rows4_most_models(D, K, M):
 @pytest.mark.parametrize("D,M", [(4, 3), (7, 5), (16, 12), (24, 6), (64, 9)])
 def test_rows_variants(D, M):
     """The same-model weight and windows switched off on frontiers without
-    windows stay in the row kernels."""
+    windows: the row kernel for 9 to 16 devices, else the general kernel."""
     w = _rows_workload(60 + D, D=D, M=M, K=4, n=60, p_edge=0.08)
     for p in (dict(lam_m=0.3), dict(lam_m=2.0, lam_s=0.5, no_windows=1), dict(no_windows=1)):
         print("[rows] variants", D, p, flush=True)
@@ -141,7 +144,7 @@ def test_lane_topk(D, k):
     against the rule (score descending, index ascending), with ties, padding
     and unaligned scores, outputs and strides."""
     import torch
-    from paper_2605_07238_amd import fate, parity
+    from paper_2605_07238_amd import parity
     w = _rows_workload(80 + D, B=5, D=D, M=3, K=2, n=300, p_edge=0.005)
     print("[rows] lane top-k", D, k, flush=True)
     pk = fate.fate_pack_dags(w)
@@ -164,3 +167,79 @@ def test_lane_topk(D, k):
             assert np.array_equal(out_i[p].cpu().numpy(), want)
             vals = np.where(want >= 0, x[p][np.minimum(off[:-1, None] + np.maximum(want, 0), C - 1)], -np.inf)
             assert np.array_equal(out_v[p].cpu().numpy(), vals.astype(np.float32))
+
+
+def _equal_rows(D, roots, kids, x):
+    """`roots` frontier stages, each parent of all `kids` horizon stages, every
+    run time x on every device and nothing else in a cost: a row costs x."""
+    n = roots + kids
+    par_off = np.concatenate([np.zeros(roots + 1), roots * np.arange(1, kids + 1)]).astype(np.int64)
+    w = synth.make_random_small(3, B=1, n=n, D=D, M=2, K=1, H=1, max_shard=1, shard_frac=0.0, p_edge=0.0)
+    zero = np.zeros(n, np.float32)
+    w = dataclasses.replace(
+        w, par_off=par_off, par_idx=np.tile(np.arange(roots, dtype=np.int32), kids), model=np.zeros(n, np.int32),
+        elig=np.full(n, (1 << D) - 1, np.uint64), status=np.zeros(n, np.uint8), holders=np.zeros(n, np.uint64),
+        prefix_hash=np.zeros(n, np.uint64), prefix_tokens=zero, out_bytes=zero, exec=np.full((2, D), x, np.float32),
+        weight_bytes=np.full(2, 1, np.int64), cap_bytes=np.full(D, 4, np.int64), resident=np.ones((1, D), np.uint64),
+        tau_free=np.zeros((1, D), np.float32), t_now=np.zeros(1, np.float32))
+    w.params.update(gamma=1.0, no_windows=1, lam_c=0.0)
+    return w
+
+
+@pytest.mark.parametrize("D,roots,kids", [(3, 128, 1000), (8, 128, 1000), (12, 128, 1000), (16, 128, 1000), (24, 128, 1000),
+                                          (64, 128, 1000), (16, 1, 4080), (16, 1, 4081), (16, 3, 2048)])
+def test_windows_off_keeps_short_sums(D, roots, kids):
+    """A set with windows switched off is summed as the general kernel sums:
+    every row in fp64, or sixteen rows in fp32 for 9 to 16 devices.  x loses
+    just under half a last place (2^-16 of 2^-15) each time it is added to an
+    fp32 sum between 256 and 512, so one sum of all rows is off by 6e-6; x is
+    exact in sums below 16, and a row's value and the score are rounded a
+    few times each (at most eight), each by 2^-24."""
+    x = 1.0 + 2.0 ** -16 - 2.0 ** -19
+    w = _equal_rows(D, roots, kids, x)
+    print("[rows] windows off, equal rows", D, roots, kids, flush=True)
+    got = run_gpu(w, k=4)
+    want = -np.float64(x) * (1 + kids)
+    bound = (8 + (16 if 8 < D <= 16 else 0)) * 2.0 ** -24
+    assert np.abs(got["psi"] / want - 1.0).max() <= bound
+
+
+@pytest.mark.parametrize("D", [9, 12, 16])
+def test_windows_off_over_many_rows(D):
+    """Chunks cut where their stages have more rows than sixteen to a task."""
+    w = _rows_workload(70 + D, B=3, D=D, M=5, K=4, n=500, p_edge=0.03)
+    p = dict(no_windows=1)
+    print("[rows] windows off, many rows", D, flush=True)
+    for k in (4, 7):
+        check_against_oracle(w, run_gpu(w, k=k, params=p), k=k, params=p)
+    # through the sweep, beside a plain set and one with the weight: each set as alone
+    import torch
+    pk = fate.fate_pack_dags(w)
+    st = fate.fate_pack_state(pk, w)
+    sets = [fate.make_params(w, **q) for q in (dict(), p, dict(lam_m=0.5), dict(no_windows=1, lam_m=0.5))]
+    sweep = fate.fate_score_sweep(pk, st, sets)[:, :st.n_cand].cpu().numpy()
+    for i, q in enumerate(sets):
+        one = fate.fate_score_frontier(pk, st, q)[:st.n_cand].cpu().numpy()
+        assert np.array_equal(one.view(np.uint32), sweep[i].view(np.uint32)), i
+
+
+@pytest.mark.parametrize("D", [4, 8, 20, 64])
+@pytest.mark.parametrize("lam_m", [1e3, 1e5])
+def test_same_model_weight_leaves_other_terms_exact(D, lam_m):
+    """A frontier stage whose Load evicts its child's model on the child's one
+    device: placed there, no term of its score holds the same-model weight, and
+    the score has the accuracy of its own terms (at most eight roundings of
+    2^-24).  (For 9 to 16 devices the cost tables hold a switch term and its
+    difference, in which the weight cancels to its own last place.)"""
+    import builders
+    inst = dict(parents=[[], [0]], model=[0, 1], elig=[(1 << D) - 1, 1], out_bytes=[0.0, 0.0], status=[0, 0], holders=[0, 0],
+                resident=[2] + [1] * (D - 1), tau_free=[0.0] * D, t_now=0.0)
+    spec = dict(D=D, M=2, K=1, exec=[[1.1] * D, [1.3] * D], switch_s=[[0.7] * D, [0.9] * D], weight_gb=[10, 10], cap_gb=[15] * D,
+                beta=[[0.0 if i == j else 1e-10 for j in range(D)] for i in range(D)], max_shard=1, instances=[inst])
+    w = builders.from_spec(spec, H=1)
+    p = dict(lam_m=lam_m, lam_s=1.0, gamma=0.9)
+    print("[rows] same-model weight", D, lam_m, flush=True)
+    got = run_gpu(w, k=2, params=p)
+    want = oracle.score(w, params=p)["psi"]
+    assert abs(want[0]) < 5.0 and abs(got["psi"][0] / want[0] - 1.0) <= 8 * 2.0 ** -24
+    check_against_oracle(w, got, k=2, params=p)
