@@ -2826,6 +2826,8 @@ struct ScoreShape {
 // with kScoreBlock (8- to 32-lane groups): twice the lane groups per slice.
 constexpr int kScoreBlock2 = 512;
 
+constexpr int kCus = 256;  // compute units
+
 // 16-lane groups with uniform beta and at most 32 models take the slot
 // layout; 64-lane groups take the first of (heavy-stage parts, 1024 threads),
 // (no parts, 1024 threads), (no parts, 512 threads) whose LDS fits.  False if
@@ -2931,16 +2933,24 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
         if (a.nsets == 0) return;
     }
     const int G = group_width(a.D);
-    // Wide workgroups while one per instance is resident at once (two of 512
-    // threads per compute unit by registers, fewer where their LDS does not
-    // fit): fork-join-sized slices keep every group busy either way, small
-    // ones (eight stages on eight 32-lane groups) gain a second group per stage
-    // (333 layered instances on 24 devices with tiered links: 54 to 38 us with
-    // the rest of the one-shot path).  The rule reads nothing that differs
-    // between a plain and a planning state, or between a sweep and its single
-    // calls: which rows share a part decides the rounding of their sum.
+    // Wide workgroups (512 threads, twice the lane groups per slice): a small
+    // slice gains the second half of the groups in one shot, but two of them
+    // fill a compute unit's registers where five of 256 threads of the slot
+    // layout (four of the general one) share it, so many large slices lose.
+    //   general layout: while one per instance is resident at once.  On 24
+    //     devices with windows 150 to 512 layered instances take 30 to 31 us
+    //     (39 to 41 narrow), fork-join 64 x 3,000 stages 173 (201), 512 x 1,000
+    //     222 (201); with tiered links on 12, 512 x 1,000, 158 (131).
+    //   slot layout: while every slice that the instances can have, frontiers
+    //     of all their stages, has a compute unit to itself.  30 layered
+    //     instances on 16 devices with windows 15.4 us (17.9); by the number of
+    //     instances alone, 512 fork-join ones took 106 (79).
+    // The rule reads nothing that differs between a plain and a planning state,
+    // or between a sweep and its single calls: which rows share a part decides
+    // the rounding of their sum.
     const int64_t per_cu = std::min<int64_t>(2, (int64_t)(kLdsLimit / (sh.lds2 ? sh.lds2 : kLdsLimit + 1)));
-    const bool wide = G >= 8 && G <= 32 && a.B <= 256 * per_cu;
+    const int64_t most_slices = a.B * ((a.max_stages + a.slice - 1) / a.slice);
+    const bool wide = G >= 8 && G <= 32 && (sh.slots ? per_cu > 0 && most_slices <= 2 * kCus : a.B <= kCus * per_cu);
     const dim3 grid((unsigned)a.n_slices, (unsigned)a.nsets), block((unsigned)(wide ? kScoreBlock2 : sh.block));
     const size_t lds = wide ? sh.lds2 : sh.lds;
     bool var = a.topo != 0;
