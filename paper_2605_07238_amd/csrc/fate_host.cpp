@@ -1161,6 +1161,8 @@ static fate_status_t score_impl(const fate_dags_t *dags, const fate_state_h *sta
     a.topo = dags->levels == FATE_LEVELS_TOPO ? 1 : 0;
     a.Hpack = dags->H;
     a.max_stages = dags->max_stages;
+    a.N = dags->N;
+    a.n_desc = dags->n_desc;
     // a window needs a stage with R(v) > 1, a shard cap above 1 and two devices
     a.singles = std::min(std::min(dags->max_r, state->max_shard), dags->D) <= 1 ? 1 : 0;
     a.nsets = P;

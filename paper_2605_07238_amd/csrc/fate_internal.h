@@ -91,6 +91,7 @@ struct ScoreLaunch {
     int32_t Hpack;      // horizon the descendant lists were packed with
     int32_t singles;    // every frontier stage has only single-device candidates
     int64_t max_stages; // stages of the largest instance
+    int64_t N, n_desc;  // stages and horizon rows of the batch
     int32_t nsets;
     ParamSet ps[kMaxSets];
     int32_t set_of[kMaxSets];  // grid row y scores parameter set set_of[y] (its place in the output)

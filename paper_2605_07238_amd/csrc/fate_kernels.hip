@@ -674,13 +674,14 @@ __device__ __forceinline__ bool child_of(const ScoreLaunch &a, const StageRec &r
 // parameter set of the launch uses a variant.  SPLIT (64-lane groups) scores
 // heavy stages in parts; BLK is the workgroup size.  The launcher takes the
 // first of (split, score_block(G)), (no split, score_block(G)), (no split,
-// half that) whose LDS plan fits a workgroup.
-template <int G, bool UNI, bool SLOTS, bool VAR, bool SPLIT, int BLK>
+// half that) whose LDS plan fits a workgroup.  ONE compiles in the one-shot
+// scoring of small slices.
+template <int G, bool UNI, bool SLOTS, bool VAR, bool SPLIT, int BLK, bool ONE = !SPLIT>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(SLOTS ? 5 : BLK == 512 && G == 64 ? 2 : 4)))
 void k_score(ScoreLaunch a) {
     constexpr int kBlock = BLK;  // threads of this workgroup
     static_assert(!SLOTS || (UNI && G == 16), "the slot layout needs 16-lane groups and uniform beta");
-    static_assert(!SPLIT || (G == 64 && !SLOTS), "heavy-stage parts are for 64-lane groups");
+    static_assert(!SPLIT || (G == 64 && !SLOTS && !ONE), "heavy-stage parts are for 64-lane groups, and dealt their own way");
     // a planning state is launched over its slice capacity; the current
     // number of slices is on the device
     const uint32_t slice = blockIdx.x;
@@ -715,7 +716,7 @@ void k_score(ScoreLaunch a) {
     // stages on 16 devices with windows, 24.8 -> 21.3 us.  A workgroup there
     // spends 6.4 us in its prologue, 7.2 on the rows, 3.8 on the scores and top-k.
     constexpr int kDeal = kBlock / G < 64 ? kBlock / G : 64;  // groups that rows are dealt to
-    const bool oneshot = !kSplit && nF <= kDeal;
+    const bool oneshot = ONE && nF <= kDeal;
 
     Lds L;
     L.logT = table_log2(D, K);
@@ -2827,6 +2828,7 @@ struct ScoreShape {
 constexpr int kScoreBlock2 = 512;
 
 constexpr int kCus = 256;  // compute units
+constexpr int64_t kDealRows = 5;  // horizon rows a stage from which the slot layout deals small slices
 
 // 16-lane groups with uniform beta and at most 32 models take the slot
 // layout; 64-lane groups take the first of (heavy-stage parts, 1024 threads),
@@ -2942,15 +2944,23 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
     //     (39 to 41 narrow), fork-join 64 x 3,000 stages 173 (201), 512 x 1,000
     //     222 (201); with tiered links on 12, 512 x 1,000, 158 (131).
     //   slot layout: while every slice that the instances can have, frontiers
-    //     of all their stages, has a compute unit to itself.  30 layered
-    //     instances on 16 devices with windows 15.4 us (17.9); by the number of
-    //     instances alone, 512 fork-join ones took 106 (79).
-    // The rule reads nothing that differs between a plain and a planning state,
+    //     of all their stages, is resident at once (they seldom have a quarter
+    //     of those), and slices are dealt at all.  30 layered instances on 16 devices with windows 15.4 us
+    //     (17.9); by the number of instances alone, 512 fork-join ones took
+    //     106 (79).
+    // The slot layout deals its small slices from kDealRows horizon rows a stage:
+    // with fewer the second pass and its barrier cost more than the shorter
+    // chains give.  100 layered instances on 12 devices with windows, by rows a
+    // stage: 2.4, 13.6 us dealt (12.0 not); 7.3, 14.5 (15.7); 16, 15.5 (19.6).
+    // (The general layout gains from the first rows on: 2.4, 13.9 on 6 devices,
+    // 17.0.)
+    // The rules read nothing that differs between a plain and a planning state,
     // or between a sweep and its single calls: which rows share a part decides
     // the rounding of their sum.
     const int64_t per_cu = std::min<int64_t>(2, (int64_t)(kLdsLimit / (sh.lds2 ? sh.lds2 : kLdsLimit + 1)));
     const int64_t most_slices = a.B * ((a.max_stages + a.slice - 1) / a.slice);
-    const bool wide = G >= 8 && G <= 32 && (sh.slots ? per_cu > 0 && most_slices <= 2 * kCus : a.B <= kCus * per_cu);
+    const bool deal = a.n_desc >= kDealRows * a.N;  // slot layout
+    const bool wide = G >= 8 && G <= 32 && (sh.slots ? deal && per_cu > 0 && most_slices <= 2 * kCus : a.B <= kCus * per_cu);
     const dim3 grid((unsigned)a.n_slices, (unsigned)a.nsets), block((unsigned)(wide ? kScoreBlock2 : sh.block));
     const size_t lds = wide ? sh.lds2 : sh.lds;
     bool var = a.topo != 0;
@@ -2966,8 +2976,10 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
             if (UNI && sh.slots) {
                 if (wide && var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B2>), grid, block, lds, s, a);
                 else if (wide) hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B2>), grid, block, lds, s, a);
-                else if (var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0>), grid, block, lds, s, a);
-                else hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B0>), grid, block, lds, s, a);
+                else if (deal && var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0>), grid, block, lds, s, a);
+                else if (deal) hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B0>), grid, block, lds, s, a);
+                else if (var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0, false>), grid, block, lds, s, a);
+                else hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B0, false>), grid, block, lds, s, a);
             } else if (wide) {
                 hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B2>), grid, block, lds, s, a);
             } else {
