@@ -1382,12 +1382,14 @@ void k_score(ScoreLaunch a) {
                 if (nb < G) break;  // past the horizon depth or the list end
             }
 
+            int ln = lane;  // opaque, so that addresses from it are not kept in registers over the rows
+            asm volatile("" : "+v"(ln));
             if (rows_only) {  // uniform over the block: the group leaves its sums in its own staging slots
                 double *sum = reinterpret_cast<double *>(areaS);
                 if (active) {
-                    sum[lane] = acc0;
+                    sum[ln] = acc0;
 #pragma unroll
-                    for (int s = 0; s < 3; ++s) sum[(s + 1) * G + lane] = w_acc[s];
+                    for (int s = 0; s < 3; ++s) sum[(s + 1) * G + ln] = w_acc[s];
                 }
                 __syncthreads();
                 pass = 1;
@@ -1396,14 +1398,14 @@ void k_score(ScoreLaunch a) {
             if (oneshot)  // the stage's parts in row order
                 for (int q = 0; q < (int)sv.parts; ++q) {
                     const double *sum = reinterpret_cast<const double *>(static_cast<uint8_t *>(L.entries) + ((int)sv.part0 + q) * kSlotGroupBytes);
-                    acc0 += sum[lane];
+                    acc0 += sum[ln];
 #pragma unroll
-                    for (int s = 0; s < 3; ++s) w_acc[s] += sum[(s + 1) * G + lane];
+                    for (int s = 0; s < 3; ++s) w_acc[s] += sum[(s + 1) * G + ln];
                 }
 
             // ---- emit scores
             const float psi0 = feas_v ? (float)(-((double)j0_single + acc0)) : -inf_f();
-            if (live) scores[c0 + lane] = psi0;
+            if (live) scores[c0 + ln] = psi0;
             uint32_t off = c0 + (uint32_t)D;
             float psiw[3] = {-inf_f(), -inf_f(), -inf_f()};
 #pragma unroll
@@ -1411,7 +1413,7 @@ void k_score(ScoreLaunch a) {
                 if (s >= nk) break;  // uniform
                 const int k = s + 2;
                 psiw[s] = w_ok[s] ? (float)(-((double)w_j0[s] + w_acc[s])) : -inf_f();
-                if (lane <= D - k) scores[off + lane] = psiw[s];
+                if (ln <= D - k) scores[off + ln] = psiw[s];
                 off += (uint32_t)(D - k + 1);
             }
             // ---- fused top-k: the group ranks the scores it holds (the same
@@ -1426,28 +1428,28 @@ void k_score(ScoreLaunch a) {
                 // a stage ranked here marks the slot instead
                 uint32_t *ranked = reinterpret_cast<uint32_t *>(L.stages + si);
                 if (a.topk <= kLaneTopk && __ballot(nk != 0) == 0ull) {  // uniform over the wave
-                    ranked[lane] = live ? topk_bits(psi0) : 0u;
+                    ranked[ln] = live ? topk_bits(psi0) : 0u;
                     continue;
                 }
-                if (lane == 0) ranked[0] = kRankedInLoop;
+                if (ln == 0) ranked[0] = kRankedInLoop;
                 if (__ballot(nk != 0) == 0ull) {  // uniform over the wave: singletons only
                     uint32_t sb[1] = {live ? topk_bits(psi0) : 0u};
-                    const uint32_t ci[1] = {(uint32_t)lane};
-                    group_topk_at<G, 1>(sb, ci, lane, a.topk, ti, tv);
+                    const uint32_t ci[1] = {(uint32_t)ln};
+                    group_topk_at<G, 1>(sb, ci, ln, a.topk, ti, tv);
                 } else {
                     uint32_t sb[4], ci[4];
                     sb[0] = live ? topk_bits(psi0) : 0u;
-                    ci[0] = (uint32_t)lane;
+                    ci[0] = (uint32_t)ln;
                     uint32_t base_c = (uint32_t)D;
 #pragma unroll
                     for (int s = 0; s < 3; ++s) {
                         const int k = s + 2;
-                        const bool has = s < nk && lane <= D - k;
+                        const bool has = s < nk && ln <= D - k;
                         sb[s + 1] = has ? topk_bits(psiw[s]) : 0u;
-                        ci[s + 1] = has ? base_c + (uint32_t)lane : 0xfffffff0u + (uint32_t)s;  // distinct, never picked
+                        ci[s + 1] = has ? base_c + (uint32_t)ln : 0xfffffff0u + (uint32_t)s;  // distinct, never picked
                         base_c += s < nk ? (uint32_t)(D - k + 1) : 0u;
                     }
-                    group_topk_at<G, 4>(sb, ci, lane, a.topk, ti, tv);
+                    group_topk_at<G, 4>(sb, ci, ln, a.topk, ti, tv);
                 }
             }
             continue;
