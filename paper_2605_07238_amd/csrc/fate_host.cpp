@@ -1331,6 +1331,7 @@ static void sim_fill(const fate_dags_t *dags, const fate_state_h *state, float k
     a.M = dags->M;
     a.ch_off = dags->ch_off;
     a.max_stages = dags->max_stages;
+    a.N = dags->N;
     a.beta_uniform = dags->beta_uniform;
     a.beta0 = dags->beta0;
     // the mean of D (D - 1) equal coefficients, summed one by one as for others

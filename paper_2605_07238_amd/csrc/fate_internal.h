@@ -295,7 +295,7 @@ struct SimLaunch {
     uint8_t *flags;
     double kpf;
     const uint32_t *ch_off;  // stage g has children if ch_off[g] < ch_off[g + 1]
-    int64_t max_stages;      // stages of the largest instance
+    int64_t max_stages, N;   // stages of the largest instance, of the batch
     double bmean;            // mean off-diagonal transfer coefficient (uniform beta)
     float beta0;             // every off-diagonal coefficient (uniform beta)
     int32_t beta_uniform;

@@ -1056,24 +1056,49 @@ __global__ __launch_bounds__(64) void k_sim_lds(SimLaunch a) {
 
 }  // namespace
 
-// Whether an instance of the batch's largest size fits the LDS of k_sim_lds:
-// 20 to 32 bytes per stage (29 KB in all for 1,000 stages on 16 devices).
-// Larger instances walk through the workspace in k_sim, the only place that
-// holds them.  Fork-join, 1,024 instances of 1,000 stages (700 to run) on 16
+// Whether a batch takes k_sim_lds.  The choice is the batch's: its largest
+// instance has to fit the LDS (20 to 32 bytes per stage and the tables: 29 KB
+// for 1,000 stages on 16 devices), or all of its instances walk through the
+// workspace in k_sim, the only place that holds the large one: 1,023 instances
+// of 200 stages beside one of 9,000 are placed in 73.5 ms, as long as the large
+// one takes.  Fork-join, 1,024 instances of 1,000 stages (700 to run) on 16
 // devices, one wave per SIMD: HEFT placement 6.44 ms in k_sim, 0.65 ms here;
 // execution 3.60 ms, 0.66 ms.  Of the 0.65 ms the walk takes 0.53 (1,700 cycles
 // a stage: arrivals 500, finish and choice 300, Load and slots 450), the
 // ranks 0.04 and the sort 0.05; the chain of single instructions binds, not
 // memory.
-static bool sim_lds_fits(const SimLaunch &a) {
-    return a.ch_off && a.max_stages <= 16384 && sim_plan(a.max_stages, a.D, a.K, a.M, a.beta_uniform != 0).total <= 160 * 1024;
+//
+// k_sim keeps eight walks per compute unit whatever their size.  While the LDS
+// leaves room for two, k_sim_lds is ahead also of that (4,096 layered instances
+// of 1,500 stages on 48 devices with links of two speeds, execution 11.6 ms
+// against 12.3).  With room for one, placement stays ahead (2,048 power-law
+// instances of 4,000 stages on 64 devices 28.8 ms against 57.4), and execution,
+// whose link in k_sim is shorter, while few instances are many rounds of one
+// per compute unit, or where the devices are few.  Execution in ms, k_sim_lds
+// and k_sim, 4,000 stages, uniform links:
+//   64 devices, power-law  1,024 instances 12.1, 18.4; 1,536 18.2, 20.0; 2,048 24.3, 20.9
+//   32 devices, 2,048      power-law 21.1, 21.0; layered 20.7, 19.4
+//   24 devices             layered 2,048 19.5, 19.1; power-law 4,096 40.7, 41.9
+//   16 devices, fork-join  4,096 39.9, 53.7
+// and with links of several speeds, where the walk reads the link of every
+// holder:
+//   64 devices, power-law, 2,500 stages  1,024 9.5, 10.5; 1,280 11.9, 11.1; 2,048 19.3, 12.2
+//   2,048 of 4,000 stages  16 devices, layered 25.2, 19.1; 8 devices 17.5, 18.9
+static bool sim_in_lds(const SimLaunch &a, int mode) {
+    constexpr int kCus = 256, kLds = 160 * 1024;
+    const bool uni = a.beta_uniform != 0;
+    if (!a.ch_off || a.max_stages > 16384) return false;
+    const uint32_t lds = sim_plan(a.max_stages, a.D, a.K, a.M, uni).total;
+    if (lds > (uint32_t)kLds) return false;
+    const bool few = a.D <= (uni ? 24 : 8);
+    return mode == 2 || lds <= (uint32_t)kLds / 2 || few || a.N <= (uni ? 6 : 4) * kCus * a.max_stages;
 }
 
 int launch_sim(const SimLaunch &a, int mode, void *stream) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (a.B <= 0) return 0;
     const dim3 grid((unsigned)a.B), block(64);
-    if (mode != 1 && sim_lds_fits(a)) {
+    if (mode != 1 && sim_in_lds(a, mode)) {
         const bool uni = a.beta_uniform != 0;
         const size_t lds = sim_plan(a.max_stages, a.D, a.K, a.M, uni).total;
         if (mode == 0) {

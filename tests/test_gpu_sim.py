@@ -240,3 +240,32 @@ def test_device_walk_edges(name, make):
         got, host = _run_device(w, pk, st, dev, order), fate.fate_simulate(w, dev, order)
         for k in got:
             assert np.array_equal(got[k], host[k]), k
+
+
+def test_device_execution_many_large_instances():
+    """A batch whose instances leave one per compute unit in LDS, and more of
+    them than are worth that many rounds: the execution takes the workspace,
+    the placement the LDS.  Both equal the host's on the repeated instances."""
+    pool, B, n = 5, 1030, 520
+    rc = dict(synth.RECIPES["powerlaw-256x10000-d64"])
+    rc.update(n=n, D=64, M=64, H=0)
+    cluster = synth.make_cluster(rc, 3)
+    srv = np.arange(64) // 8
+    beta = np.where(srv[:, None] == srv[None, :], 1e-10, 5e-10).astype(np.float32)
+    np.fill_diagonal(beta, 0.0)
+    cluster = cluster[:4] + (beta,)
+    insts = [synth._gen_instance(rc, cluster, 3, b, 32, 4) for b in range(pool)]
+    small = synth._assemble("pool", rc, cluster, insts, 32, 4)
+    w = synth._assemble("many", rc, cluster, insts * (B // pool), 32, 4)
+    # 70,656 bytes of tables and 32 or less a stage: more than half of 160 KB, less than all
+    assert 81920 < 70656 + 8 * n + 12 * 1024 < 163840 and w.N > 4 * 256 * n
+    pk, st = _packed(w)
+    print("[sim] many large instances", w.N, flush=True)
+    kpf = w.params["kappa_prefix"]
+    dt, ot = fate.fate_place_baseline_device(pk, st, fate.FATE_PLACE_HEFT, kpf)
+    hdev, hord = fate.fate_place_baseline(small, fate.FATE_PLACE_HEFT)
+    assert np.array_equal(dt.cpu().numpy().view(np.uint64), np.tile(hdev, B // pool))
+    assert np.array_equal(ot.cpu().numpy(), np.tile(hord, B // pool))
+    got, host = fate.fate_simulate_device(pk, st, dt, ot, kpf), fate.fate_simulate(small, hdev, hord)
+    for k in got:
+        assert np.array_equal(got[k], np.tile(host[k], B // pool)), k
