@@ -2830,6 +2830,7 @@ struct ScoreShape {
 constexpr int kScoreBlock2 = 512;
 
 constexpr int kCus = 256;  // compute units
+constexpr int64_t kWideStages = 448;  // general layout: larger instances take one wide workgroup per compute unit
 constexpr int64_t kDealRows = 5;  // horizon rows a stage from which the slot layout deals small slices
 
 // 16-lane groups with uniform beta and at most 32 models take the slot
@@ -2941,10 +2942,17 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
     // slice gains the second half of the groups in one shot, but two of them
     // fill a compute unit's registers where five of 256 threads of the slot
     // layout (four of the general one) share it, so many large slices lose.
-    //   general layout: while one per instance is resident at once.  On 24
-    //     devices with windows 150 to 512 layered instances take 30 to 31 us
-    //     (39 to 41 narrow), fork-join 64 x 3,000 stages 173 (201), 512 x 1,000
-    //     222 (201); with tiered links on 12, 512 x 1,000, 158 (131).
+    //   general layout: while one per instance is resident at once, one on a
+    //     compute unit where instances of kWideStages stages or more can have
+    //     frontiers far past the groups.  On 24 devices with windows 256 to 512
+    //     layered instances of 300 stages take 34 to 35 us (51 to 53 narrow),
+    //     256 of 1,000 35 (42); fork-join, 512 of 1,000 stages 222 (191; on 32
+    //     devices 240, 191), 512 of 500 173 (143), 256 of 1,000 163 (158), 512
+    //     of 250 93 (79).  With tiered links on 12, fork-join, 512 of 1,000 155
+    //     (119), 512 of 400 91 (109); on 6 devices with windows, 512 of 400 49
+    //     (98).  On 8 devices with the mean per level, fork-join, 384 of 1,000
+    //     119 (112).  Many layered instances of kWideStages and more lose by
+    //     the line (512 of 1,000 on 24 devices, 36, narrow 45).
     //   slot layout: while every slice that the instances can have, frontiers
     //     of all their stages, is resident at once (they seldom have a quarter
     //     of those), and slices are dealt at all.  30 layered instances on 16 devices with windows 15.4 us
@@ -2962,7 +2970,8 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
     const int64_t per_cu = std::min<int64_t>(2, (int64_t)(kLdsLimit / (sh.lds2 ? sh.lds2 : kLdsLimit + 1)));
     const int64_t most_slices = a.B * ((a.max_stages + a.slice - 1) / a.slice);
     const bool deal = a.n_desc >= kDealRows * a.N;  // slot layout
-    const bool wide = G >= 8 && G <= 32 && (sh.slots ? deal && per_cu > 0 && most_slices <= 2 * kCus : a.B <= kCus * per_cu);
+    const bool wide = G >= 8 && G <= 32 && (sh.slots ? deal && per_cu > 0 && most_slices <= 2 * kCus
+                                                              : a.B <= kCus * (a.max_stages < kWideStages ? per_cu : std::min<int64_t>(1, per_cu)));
     const dim3 grid((unsigned)a.n_slices, (unsigned)a.nsets), block((unsigned)(wide ? kScoreBlock2 : sh.block));
     const size_t lds = wide ? sh.lds2 : sh.lds;
     bool var = a.topo != 0;

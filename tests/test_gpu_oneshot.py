@@ -48,6 +48,16 @@ def test_many_instances(D):
     check_against_oracle(w, run_gpu(w, k=4), k=4)
 
 
+@pytest.mark.parametrize("n", [447, 448])
+def test_large_instances(n):
+    """More instances than compute units, just below and from the size where
+    they no longer take wide workgroups."""
+    w = synth.make_random_small(8, B=257, n=n, D=20, M=4, K=2, H=1, p_edge=0.004, shard_frac=0.1, max_shard=2)
+    print("[oneshot] 257 instances of", n, flush=True)
+    assert np.diff(w.stage_off).max() == n
+    check_against_oracle(w, run_gpu(w, k=4), k=4)
+
+
 def test_nothing_to_move():
     w = synth.make_random_small(9, B=3, n=30, D=10, M=4, K=3, H=3, shard_frac=0.5)
     w.out_bytes[::2] = 0.0
