@@ -164,7 +164,7 @@ template <int G>
 using MaskFor = typename std::conditional<(G <= 32), uint32_t, uint64_t>::type;
 
 struct Lds {
-    uint64_t *pkey, *rm, *rho, *fits, *wt, *cap, *keys;
+    uint64_t *pkey, *rho, *fits, *wt, *cap, *keys;
     void *pmask;  // device masks of the prefix table: uint32_t when D <= 32, else uint64_t
     uint8_t *order;
     float *wait, *exec, *ksw, *gpow;
@@ -196,7 +196,7 @@ struct alignas(16) CostS {
 
 // Byte offsets of every LDS array (shared by the launcher and the kernel).
 struct LdsPlan {
-    uint32_t pkey, pmask, rm, rho, fits, wt, cap, order, wait, gpow, next, exec, ksw, stages, entries, total;
+    uint32_t pkey, pmask, rho, fits, wt, cap, order, wait, gpow, next, exec, ksw, stages, entries, total;
     uint32_t items, parts, left, pbase, plen, pool;  // row splits of heavy stages (64-lane groups)
     uint32_t rnew;              // general layout, at most 32 devices: residency after each load
     uint32_t btab, brow, bstr;  // non-uniform beta, at most 32 devices: see beta_table
@@ -234,7 +234,6 @@ __host__ __device__ inline LdsPlan lds_plan(int D, int K, int M, int slice, int 
     q.pkey = o; o += 8 * T;
     q.pmask = o; o += mask_bytes * T;
     o = (o + 7u) & ~7u;
-    q.rm = o; o += 8 * (uint32_t)M;
     q.rho = o; o += 8 * (uint32_t)D;
     q.fits = o; o += 8 * (uint32_t)M;
     q.wt = o; o += 8 * (uint32_t)M;
@@ -723,7 +722,6 @@ void k_score(ScoreLaunch a) {
     const int T = 1 << L.logT;
     L.pkey = reinterpret_cast<uint64_t *>(sb + plan.pkey);
     L.pmask = sb + plan.pmask;
-    L.rm = reinterpret_cast<uint64_t *>(sb + plan.rm);
     L.rho = reinterpret_cast<uint64_t *>(sb + plan.rho);
     L.fits = reinterpret_cast<uint64_t *>(sb + plan.fits);
     L.order = sb + plan.order;
@@ -806,7 +804,7 @@ void k_score(ScoreLaunch a) {
             L.stages[i] = st;
             key = ((uint64_t)(0xffffffffu - (st.e1 - st.e0)) << 32) | (uint32_t)i;
         }
-        L.keys[i] = key;
+        if (!oneshot) L.keys[i] = key;
     }
     // prefix-cache entries are fetched before the barrier and inserted after it
     constexpr int kPre = 4;
@@ -823,12 +821,6 @@ void k_score(ScoreLaunch a) {
     for (int i = tid + kPre * kBlock; i < D * K; i += kBlock) {  // D*K > 1024 only
         const uint64_t h = a.pcache[(int64_t)b * D * K + i];
         if (h != 0) table_insert<Mask>(L, h, i / K);
-    }
-    if (tid < M) {
-        uint64_t m = 0;
-        for (int d = 0; d < D; ++d)
-            if (bit(L.rho[d], tid)) m |= 1ull << d;
-        L.rm[tid] = m;
     }
     if constexpr (SLOTS) {  // residency of d after loading m, from the LDS tables (the Load rule's chain of reads)
         uint32_t *rnew = reinterpret_cast<uint32_t *>(L.ksw);
@@ -1931,7 +1923,6 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
             sw0 = a.exec[j] + swo;
             CostS c;
             c.sw0 = sw0;
-            c.ksr = ks;
             c.exec = a.exec[j];
             c.swo = swo;
             cst[j] = c;
@@ -2984,14 +2975,18 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
             else hipLaunchKernelGGL((k_score<8, UNI, false, true, false, B0>), grid, block, lds, s, a);
             break;
         case 16:
-            if (UNI && sh.slots) {
-                if (wide && var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B2>), grid, block, lds, s, a);
-                else if (wide) hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B2>), grid, block, lds, s, a);
-                else if (deal && var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0>), grid, block, lds, s, a);
-                else if (deal) hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B0>), grid, block, lds, s, a);
-                else if (var) hipLaunchKernelGGL((k_score<16, UNI, UNI, true, false, B0, false>), grid, block, lds, s, a);
-                else hipLaunchKernelGGL((k_score<16, UNI, UNI, false, false, B0, false>), grid, block, lds, s, a);
-            } else if (wide) {
+            if constexpr (UNI) {
+                if (sh.slots) {
+                    if (wide && var) hipLaunchKernelGGL((k_score<16, true, true, true, false, B2>), grid, block, lds, s, a);
+                    else if (wide) hipLaunchKernelGGL((k_score<16, true, true, false, false, B2>), grid, block, lds, s, a);
+                    else if (deal && var) hipLaunchKernelGGL((k_score<16, true, true, true, false, B0>), grid, block, lds, s, a);
+                    else if (deal) hipLaunchKernelGGL((k_score<16, true, true, false, false, B0>), grid, block, lds, s, a);
+                    else if (var) hipLaunchKernelGGL((k_score<16, true, true, true, false, B0, false>), grid, block, lds, s, a);
+                    else hipLaunchKernelGGL((k_score<16, true, true, false, false, B0, false>), grid, block, lds, s, a);
+                    break;
+                }
+            }
+            if (wide) {
                 hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B2>), grid, block, lds, s, a);
             } else {
                 hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B0>), grid, block, lds, s, a);
