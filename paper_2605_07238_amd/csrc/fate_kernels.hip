@@ -2946,9 +2946,9 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
     //     the line (512 of 1,000 on 24 devices, 36, narrow 45).
     //   slot layout: while every slice that the instances can have, frontiers
     //     of all their stages, is resident at once (they seldom have a quarter
-    //     of those), and slices are dealt at all.  30 layered instances on 16 devices with windows 15.4 us
-    //     (17.9); by the number of instances alone, 512 fork-join ones took
-    //     106 (79).
+    //     of those), and slices are dealt at all.  30 layered instances on 16
+    //     devices with windows 15.4 us (17.9); by the number of instances
+    //     alone, 512 fork-join ones took 106 (79).
     // The slot layout deals its small slices from kDealRows horizon rows a stage:
     // with fewer the second pass and its barrier cost more than the shorter
     // chains give.  100 layered instances on 12 devices with windows, by rows a
