@@ -225,8 +225,23 @@ __host__ __device__ inline int beta_rows(int D) {
 constexpr int kSplitRows = 128, kSplitItems = 256, kSplitSlots = 32;
 static_assert(kSplitRows % 64 == 0, "a part is whole 64-row batches");
 
+// Tables of the general layout up to 32 devices (a template argument of
+// k_score).  kLoadTab: the residency of every device after loading every model,
+// for at most kLoadPairs (model, device) pairs, two a thread.  With more, every
+// workgroup prepares many that its few stages never ask for, in the LDS of a
+// second workgroup.  1,024 layered instances with windows and H = 3, with the
+// table and without: 24 models on 24 devices 58.3 and 53.3 us, 40 on 20 78.9
+// and 63.9, 64 on 32 with links of two speeds 186 and 92 (within the line, 12
+// on 24, 57.5 and 56.6, but 100 instances 27.9 and 28.5).
+// kCoefTab: the cheapest transfer coefficient from each candidate into each
+// device (non-uniform beta).  Sets without a horizon have no rows to use it on:
+// the same instances with links of two speeds and H = 0, 12 models on 24
+// devices 33.5 and 18.3 us, 16 on 32 37.2 and 26.9.
+constexpr int kLoadTab = 1, kCoefTab = 2, kLoadPairs = 512;
+inline int tables_for(int D, int M, bool uni) { return (M * D <= kLoadPairs ? kLoadTab : 0) | (uni ? 0 : kCoefTab); }
+
 __host__ __device__ inline LdsPlan lds_plan(int D, int K, int M, int slice, int staging, bool slots, bool split,
-                                            bool uni, int blk) {
+                                            int tabs, int blk) {
     LdsPlan q;
     const uint32_t T = 1u << table_log2(D, K);
     const uint32_t mask_bytes = D <= 32 ? 4u : 8u;
@@ -258,8 +273,8 @@ __host__ __device__ inline LdsPlan lds_plan(int D, int K, int M, int slice, int 
     q.bstr = (((uint32_t)D + 3u) & ~3u) + 4u;  // whole float4s; consecutive rows start on different banks
     if (!slots && D <= 32) {
         o = (o + 15u) & ~15u;
-        q.rnew = o; o += 8 * (uint32_t)(M * D);
-        if (!uni) {
+        q.rnew = o; o += (tabs & kLoadTab) ? 8 * (uint32_t)(M * D) : 0u;
+        if (tabs & kCoefTab) {
             o = (o + 15u) & ~15u;
             q.btab = o; o += 4 * q.bstr * (uint32_t)beta_rows(D);
             q.brow = o; o += 4 * (uint32_t)blk;  // a row of B per lane group
@@ -675,7 +690,8 @@ __device__ __forceinline__ bool child_of(const ScoreLaunch &a, const StageRec &r
 // first of (split, score_block(G)), (no split, score_block(G)), (no split,
 // half that) whose LDS plan fits a workgroup.  ONE compiles in the one-shot
 // scoring of small slices.
-template <int G, bool UNI, bool SLOTS, bool VAR, bool SPLIT, int BLK, bool ONE = !SPLIT>
+template <int G, bool UNI, bool SLOTS, bool VAR, bool SPLIT, int BLK, bool ONE = !SPLIT,
+          int TABS = kLoadTab | (UNI ? 0 : kCoefTab)>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(SLOTS ? 5 : BLK == 512 && G == 64 ? 2 : 4)))
 void k_score(ScoreLaunch a) {
     constexpr int kBlock = BLK;  // threads of this workgroup
@@ -703,9 +719,9 @@ void k_score(ScoreLaunch a) {
     constexpr bool kSlots = SLOTS;
     using Entry = EntryL<Mask>;
     constexpr bool kSplit = SPLIT;
-    const LdsPlan plan = lds_plan(D, K, M, a.slice, staging_bytes<G, BLK>(), SLOTS, kSplit, UNI, BLK);
+    const LdsPlan plan = lds_plan(D, K, M, a.slice, staging_bytes<G, BLK>(), SLOTS, kSplit, TABS, BLK);
     // non-uniform beta on at most 32 devices: the transfer table
-    constexpr bool kTab = !UNI && G <= 32;
+    constexpr bool kTab = !UNI && G <= 32 && (TABS & kCoefTab) != 0;
     float *btab = reinterpret_cast<float *>(sb + plan.btab);
     const int bstr = (int)plan.bstr;
     // A slice with no more stages than lane groups is scored in one shot: its
@@ -829,7 +845,8 @@ void k_score(ScoreLaunch a) {
             rnew[i] = (uint32_t)load_model(L.rho[d], m, L.cap[d], L.wt);
         }
     }
-    if constexpr (!SLOTS && G <= 32) {
+    constexpr bool kLoads = !SLOTS && G <= 32 && (TABS & kLoadTab) != 0;
+    if constexpr (kLoads) {
         uint64_t *rnew = reinterpret_cast<uint64_t *>(sb + plan.rnew);
         for (int i = tid; i < M * D; i += kBlock) {
             const int m = i / D, d = i - m * D;
@@ -1040,7 +1057,7 @@ void k_score(ScoreLaunch a) {
         float a_imm = 0.0f, b_imm = 0.0f;
         if constexpr (!kSlots) imm_terms(a_imm, b_imm);
         const uint64_t rho_new = kSlots ? (uint64_t)reinterpret_cast<const uint32_t *>(L.ksw)[mv * D + dl]
-                                 : G <= 32 ? reinterpret_cast<const uint64_t *>(sb + plan.rnew)[mv * D + dl]
+                                 : kLoads ? reinterpret_cast<const uint64_t *>(sb + plan.rnew)[mv * D + dl]
                                            : load_model(rho, mv, L.cap[dl], L.wt);
         const bool prefix_added = sv.hash != 0 && !hv_cached;
         const uint64_t feas_mask = (__ballot(feas_v) >> gbase) & gmask;
@@ -2834,11 +2851,12 @@ static bool score_shape(int D, int K, int M, int slice, bool uni, ScoreShape &sh
     sh.split = false;
     sh.lds2 = 0;
     sh.block = score_block(G);
+    const int tabs = tables_for(D, M, uni);
     if (G < 64) {
         const int sb = G == 16 ? staging_bytes<16, kScoreBlock>() : staging_bytes<8, kScoreBlock>();
-        sh.lds = lds_plan(D, K, M, slice, sb, sh.slots, false, uni, kScoreBlock).total;
+        sh.lds = lds_plan(D, K, M, slice, sb, sh.slots, false, tabs, kScoreBlock).total;
         const int sb2 = G == 16 ? staging_bytes<16, kScoreBlock2>() : staging_bytes<8, kScoreBlock2>();
-        sh.lds2 = lds_plan(D, K, M, slice, sb2, sh.slots, false, uni, kScoreBlock2).total;
+        sh.lds2 = lds_plan(D, K, M, slice, sb2, sh.slots, false, tabs, kScoreBlock2).total;
         return sh.lds <= kLdsLimit;
     }
     const bool split[3] = {true, false, false};
@@ -2846,7 +2864,7 @@ static bool score_shape(int D, int K, int M, int slice, bool uni, ScoreShape &sh
     for (int c = 0; c < 3; ++c) {
         const int sb = block[c] == score_block(64) ? staging_bytes<64, score_block(64)>()
                                                    : staging_bytes<64, score_block(64) / 2>();
-        const size_t lds = lds_plan(D, K, M, slice, sb, false, split[c], uni, block[c]).total;
+        const size_t lds = lds_plan(D, K, M, slice, sb, false, split[c], tabs, block[c]).total;
         if (lds <= kLdsLimit) {
             sh.split = split[c];
             sh.block = block[c];
@@ -2898,6 +2916,24 @@ static void launch_rows(const ScoreLaunch &a, hipStream_t s) {
         case 8: hipLaunchKernelGGL((k_rows<8, kRowsBlock>), grid, block, lds, s, a); break;
         default: hipLaunchKernelGGL((k_rows<16, kRowsBlock>), grid, block, lds, s, a); break;
     }
+}
+
+// The general layout of 16- and 32-lane groups with the tables that its sets
+// use (narrower groups always fit and use both).
+template <int G, bool UNI, int BLK>
+static void launch_tables(const ScoreLaunch &a, dim3 grid, hipStream_t s) {
+    int tabs = tables_for(a.D, a.M, UNI);
+    bool rows = false;
+    for (int p = 0; p < a.nsets; ++p) rows = rows || a.ps[p].H > 0;
+    if (!rows) tabs &= ~kCoefTab;
+    const size_t lds = lds_plan(a.D, a.K, a.M, a.slice, staging_bytes<G, BLK>(), false, false, tabs, BLK).total;
+    const dim3 block((unsigned)BLK);
+    if constexpr (!UNI) {
+        if (tabs == (kLoadTab | kCoefTab)) hipLaunchKernelGGL((k_score<G, false, false, true, false, BLK, true, kLoadTab | kCoefTab>), grid, block, lds, s, a);
+        if (tabs == kCoefTab) hipLaunchKernelGGL((k_score<G, false, false, true, false, BLK, true, kCoefTab>), grid, block, lds, s, a);
+    }
+    if (tabs == kLoadTab) hipLaunchKernelGGL((k_score<G, UNI, false, true, false, BLK, true, kLoadTab>), grid, block, lds, s, a);
+    if (tabs == 0) hipLaunchKernelGGL((k_score<G, UNI, false, true, false, BLK, true, 0>), grid, block, lds, s, a);
 }
 
 template <bool UNI>
@@ -2986,15 +3022,12 @@ static void launch_score_g(const ScoreLaunch &a0, const ScoreShape &sh, hipStrea
                     break;
                 }
             }
-            if (wide) {
-                hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B2>), grid, block, lds, s, a);
-            } else {
-                hipLaunchKernelGGL((k_score<16, UNI, false, true, false, B0>), grid, block, lds, s, a);
-            }
+            if (wide) launch_tables<16, UNI, B2>(a, grid, s);
+            else launch_tables<16, UNI, B0>(a, grid, s);
             break;
         case 32:
-            if (wide) hipLaunchKernelGGL((k_score<32, UNI, false, true, false, B2>), grid, block, lds, s, a);
-            else hipLaunchKernelGGL((k_score<32, UNI, false, true, false, B0>), grid, block, lds, s, a);
+            if (wide) launch_tables<32, UNI, B2>(a, grid, s);
+            else launch_tables<32, UNI, B0>(a, grid, s);
             break;
         default:
             if (sh.split) hipLaunchKernelGGL((k_score<64, UNI, false, true, true, B64>), grid, block, lds, s, a);

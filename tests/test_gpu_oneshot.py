@@ -58,6 +58,27 @@ def test_large_instances(n):
     check_against_oracle(w, run_gpu(w, k=4), k=4)
 
 
+@pytest.mark.parametrize("D,M", [(16, 32), (16, 33), (24, 21), (24, 22), (32, 16), (32, 17), (32, 64)])
+@pytest.mark.parametrize("uniform", [True, False], ids=["uniform", "tiered"])
+def test_tables(D, M, uniform):
+    """Up to 512 (model, device) pairs the workgroup prepares every load's
+    residency, with more each stage loads its own; the transfer table is there
+    where a set of the launch has a horizon.  Tight capacities, so that loads
+    evict; each set of a sweep over the horizons writes its single call's bits."""
+    w = synth.make_random_small(60 + D + M, B=5, n=50, D=D, M=M, K=4, H=2, shard_frac=0.5, max_shard=4, p_edge=0.07,
+                                uniform_beta=uniform)
+    print("[oneshot] tables D=%d M=%d uniform=%d" % (D, M, uniform), flush=True)
+    for H in (0, 2):
+        check_against_oracle(w, run_gpu(w, H=H, k=4), H=H, k=4)
+    pk = fate.fate_pack_dags(w)
+    st = fate.fate_pack_state(pk, w)
+    sets = [fate.make_params(w, H=h) for h in (0, 1, 2)]
+    sweep = fate.fate_score_sweep(pk, st, sets)[:, :st.n_cand].cpu().numpy()
+    for p, one in zip(sets, sweep):
+        got = fate.fate_score_frontier(pk, st, p)[:st.n_cand].cpu().numpy()
+        assert np.array_equal(got.view(np.uint32), one.view(np.uint32))
+
+
 def test_nothing_to_move():
     w = synth.make_random_small(9, B=3, n=30, D=10, M=4, K=3, H=3, shard_frac=0.5)
     w.out_bytes[::2] = 0.0
